@@ -23,9 +23,29 @@
 #include <string>
 #include <vector>
 
-#include "gemm_kernel.hpp"
+#include "gemm_split.hpp"
 
 namespace cpra {
+
+namespace gemmk {
+
+// Operands that the split kernels' 32-bit offsets within a tile reach: leading
+// dimensions below 2^22 (128 rows of them stay below 2^31 bytes).
+bool split_ok(const LaunchArgs& args) {
+  const int64_t lim = int64_t(1) << 22;
+  for (int i = 0; i < args.n_prob; ++i) {
+    const ProbDev& d = args.p[i];
+    if (d.M <= 0) continue;
+    if (d.N <= 0 || d.n_eff >= lim || d.ldc >= lim || (d.mask && d.ld_mask >= lim) ||
+        (d.add && d.ld_add >= lim) || (d.sig_out && d.ld_sig >= lim))
+      return false;
+    for (int pc = 0; pc < d.n_pieces; ++pc)
+      if (d.lda[pc] >= lim || d.ldb[pc] >= lim) return false;
+  }
+  return true;
+}
+
+}  // namespace gemmk
 
 namespace {
 
@@ -96,7 +116,13 @@ const char* kCfgNames[kNumCfgs] = {"64x64x32_w2x2",   "64x64x32_w2x1", "64x64x32
                                    "64x128x16_w2x2_il", "64x64x32_w2x2_il",
                                    "64x128x32_w2x2_il", "64x64x16_w2x2_ring",
                                    "64x128x16_w2x2_ring", "128x64x16_w2x2_ring",
-                                   "64x64x32_w2x2_ring", "128x128x16_w2x2_ring"};
+                                   "64x64x32_w2x2_ring", "128x128x16_w2x2_ring",
+                                   "64x64x32_w2x2_bf3", "128x64x32_w2x2_bf3",
+                                   "64x128x32_w2x2_bf3", "128x128x32_w2x4_bf3",
+                                   "128x32x32_w4x1_bf3", "32x64x32_w1x2_bf3",
+                                   "32x32x32_w1x1_bf3", "64x64x16_w2x1_bf3", "128x128x32_rows_bf3", "128x64x32_rows_bf3", "128x32x32_rows_bf3",
+                                   "64x64x32_rows_bf3", "32x32x32_rows_bf3", "64x64x32_w2x2_ord", "128x64x32_w2x2_ord", "32x64x32_w1x2_ord",
+                                   "32x32x32_w1x1_ord", "128x128x32_w2x4_ord", "128x32x32_w4x1_ord"};
 
 struct Plan {
   int cfg, splits;
@@ -147,9 +173,47 @@ int heuristic_splits(const GemmProblem* probs, int n, const Cfg& c) {
   return max(1, min(s, kMaxSplits));
 }
 
-Plan heuristic_plan(const GemmProblem* probs, int n, bool can_split) {
-  Plan p{0, 1};
-  if (tiles_of(probs, n, kCfgs[5]) >= 1024) p.cfg = 5;
+// The plan of a shape that is not in the tuning table (us alone, three launches
+// between two events, against the 64x64x32 or 128x128x32 one-deep loop that these
+// rules replace and the best of configurations 0-31).
+//  * Ordered products (a training step's) and small launches: FP32 MFMAs over k in
+//    order, 64x64 tiles, or 32 rows where those leave fewer than 128 blocks.  Under
+//    256 blocks the matrix rate does not set the time and both kinds take the same
+//    (2,000x64, K = 128: 7.2 either way, 9.4 before).
+//  * Else the split kernels: 128x64 tiles with A in registers from 512 of them on
+//    (two per CU; 100,000x128, K = 256: 49, ordered 63, before 97, best old 78;
+//    704,000x64, K = 64: 76, 86, 190, 111), 64x64 below (10,000x256, K = 512: 25.5,
+//    ordered 31, 128x64 rows 27, before 46, best old 35).
+//  * Weight gradients: the split count brings 64x64 tiles to 512 blocks with 4 K steps
+//    at least (128x128 over K = 100,000 in 128: 39 split, 44 ordered, 41 best old);
+//    up to 32 rows of output, 32-row tiles.
+Plan heuristic_plan(bool a_t, const GemmProblem* probs, int n, bool can_split) {
+  int n_cols = 0, m_rows = 0;
+  bool ordered = false, bias_grad = false;
+  for (int i = 0; i < n; ++i) {
+    n_cols = max(n_cols, probs[i].N);
+    m_rows = max(m_rows, probs[i].M);
+    ordered = ordered || probs[i].ordered;
+    bias_grad = bias_grad || probs[i].bias_grad;
+  }
+  const int64_t tiles64 = tiles_of(probs, n, kCfgs[kOrd64]);
+  Plan p{kOrd64, 1};
+  if (can_split) p.splits = heuristic_splits(probs, n, kCfgs[kOrd64]);
+  if (ordered || tiles64 * p.splits < 256) {
+    // a bias gradient keeps the four slices per row of the 256- and 128-thread tiles
+    if (a_t) p.cfg = m_rows > 32 ? kOrd64 : n_cols > 32 || bias_grad ? kOrd32x64 : kOrd32;
+    else if (n_cols <= 32) p.cfg = tiles_of(probs, n, kCfgs[kOrd128x32]) >= 512 ? kOrd128x32 : kOrd32;
+    else p.cfg = tiles64 >= 128 ? kOrd64 : kOrd32x64;
+    return p;
+  }
+  p.cfg = kSplit64;
+  if (a_t) {
+    if (m_rows <= 32) p.cfg = n_cols <= 32 ? kSplit32 : kSplit32x64;
+  } else if (n_cols <= 32) {
+    p.cfg = tiles_of(probs, n, kCfgs[kRows128x32]) >= 512 ? kRows128x32 : kRows32;
+  } else if (tiles_of(probs, n, kCfgs[kRows128x64]) >= 512) {
+    p.cfg = kRows128x64;
+  }
   if (can_split) p.splits = heuristic_splits(probs, n, kCfgs[p.cfg]);
   return p;
 }
@@ -303,11 +367,9 @@ cpra_status run_plan(bool a_t, bool b_t, const GemmProblem* probs, int n, const 
   snprintf(pname, sizeof(pname), "gemm_%s%s_%s", layout[a_t][b_t], gmode[mode], kCfgNames[cfg]);
   {
     ProfScope ps(pname, stream, flops, 0.0);
-    if (mode) launch_grouped(mode, a_t, b_t, cfg, args, stream);
-    else if (!a_t && b_t) launch_any<false, true, 0>(cfg, args, stream);
-    else if (!a_t && !b_t) launch_any<false, false, 0>(cfg, args, stream);
-    else if (a_t && !b_t) launch_any<true, false, 0>(cfg, args, stream);
-    else launch_any<true, true, 0>(cfg, args, stream);
+    if (cfg >= kFirstSplit) launch_split(mode, a_t, b_t, cfg, args, stream);
+    else if (mode) launch_grouped(mode, a_t, b_t, cfg, args, stream);
+    else launch_plain(a_t, b_t, cfg, args, stream);
   }
   CPRA_CHECK_LAUNCH("gemm");
   if (pl.splits > 1) {
@@ -332,11 +394,12 @@ cpra_status tune(bool a_t, bool b_t, const GemmProblem* probs, int n, void* ws, 
   hipEvent_t e0, e1;
   if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess)
     CPRA_FAIL(CPRA_ERR_HIP, "gemm tune: event creation failed");
-  const Plan heur = heuristic_plan(probs, n, ws != nullptr);
+  const Plan heur = heuristic_plan(a_t, probs, n, ws != nullptr);
   const char* env = getenv("CPRA_AUTOTUNE_LOG");  // print every candidate's time
   const bool log_candidates = env != nullptr && env[0] == '1';
   TuneEntry entry{Plan{0, 1}, 1e30, -1.0};
   for (int c = 0; c < kNumCfgs; ++c) {
+    if (a_t && c >= kFirstRows && c < kFirstOrdered) continue;  // those take A [M, K]
     std::vector<int> splits;
     for (int s : split_candidates(probs, n, kCfgs[c]))
       if (s == 1 || (ws != nullptr && partial_floats(s, probs, n) * sizeof(float) <= ws_bytes))
@@ -432,7 +495,7 @@ cpra_status gemm_batch(bool a_t, bool b_t, const GemmProblem* probs_in, int n, v
     if (g_tuning && !capturing && overwrite_only)
       return tune(a_t, b_t, probs, n, can_split ? ws : nullptr, can_split ? ws_bytes : 0, stream,
                   key, &pl);
-    pl = heuristic_plan(probs, n, can_split);
+    pl = heuristic_plan(a_t, probs, n, can_split);
   }
   // A tuned plan may split more than this workspace allows: fall back to fewer splits.
   // Row-grouped products are never split (their reduction has no per-graph bias).

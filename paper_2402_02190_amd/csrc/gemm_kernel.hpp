@@ -1005,8 +1005,35 @@ constexpr Cfg kCfgs[] = {
     {128, 64, 16, 2, 2},   // 29
     {64, 64, 32, 2, 2},    // 30
     {128, 128, 16, 2, 2},  // 31
+    // three-way bfloat16 splitting (gemm_split.hpp)
+    {64, 64, 32, 2, 2},    // 32: 256 threads, 32x32 per wave
+    {128, 64, 32, 2, 2},   // 33: 64x32 per wave
+    {64, 128, 32, 2, 2},   // 34: 32x64 per wave
+    {128, 128, 32, 2, 4},  // 35: 512 threads, 64x32 per wave
+    {128, 32, 32, 4, 1},   // 36: 32x32 per wave
+    {32, 64, 32, 1, 2},    // 37: 128 threads, 32x32 per wave
+    {32, 32, 32, 1, 1},    // 38: 64 threads
+    {64, 64, 16, 2, 1},    // 39: 128 threads, 32x64 per wave
+    // the same with A loaded straight into the MFMA layout (A [M, K])
+    {128, 128, 32, 4, 1},  // 40: 256 threads, 32x128 per wave
+    {128, 64, 32, 4, 1},   // 41: 32x64 per wave
+    {128, 32, 32, 4, 1},   // 42: 32x32 per wave
+    {64, 64, 32, 2, 1},    // 43: 128 threads, 32x64 per wave
+    {32, 32, 32, 1, 1},    // 44: 64 threads
+    // FP32 MFMAs in the same structure, k in order
+    {64, 64, 32, 2, 2},    // 45
+    {128, 64, 32, 2, 2},   // 46
+    {32, 64, 32, 1, 2},    // 47
+    {32, 32, 32, 1, 1},    // 48
+    {128, 128, 32, 2, 4},  // 49
+    {128, 32, 32, 4, 1},   // 50
 };
 constexpr int kNumCfgs = sizeof(kCfgs) / sizeof(kCfgs[0]);
+constexpr int kFirstSplit = 32;  // configurations from here on are those of gemm_split.hpp
+constexpr int kFirstRows = 40;   // ... and from here on take A [M, K] (k_gemm_rows)
+constexpr int kSplit64 = 32, kSplit32x64 = 37, kSplit32 = 38, kRows128x64 = 41, kRows128x32 = 42, kRows32 = 44;
+constexpr int kFirstOrdered = 45;  // FP32 MFMAs, sums over k in order
+constexpr int kOrd64 = 45, kOrd128x64 = 46, kOrd32x64 = 47, kOrd32 = 48, kOrd128x32 = 50;
 
 // index of a row-tile height in LaunchArgs::row_maps
 constexpr int bm_index(int bm) { return bm == 32 ? 0 : bm == 64 ? 1 : 2; }
@@ -1073,15 +1100,15 @@ constexpr int kIlTwin[] = {0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15,
 // reach past the 2^31-byte offsets of its buffer loads
 constexpr int kRingTwin[] = {0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15, 16, 17, 18, 19,
                              20, 21, 22, 23, 24, 25, 26, 20, 24, 22, 25, 21};
-static_assert(sizeof(kIlTwin) / sizeof(kIlTwin[0]) == kNumCfgs, "one twin per configuration");
-static_assert(sizeof(kRingTwin) / sizeof(kRingTwin[0]) == kNumCfgs, "one twin per configuration");
+static_assert(sizeof(kIlTwin) / sizeof(kIlTwin[0]) == kFirstSplit, "one twin per configuration");
+static_assert(sizeof(kRingTwin) / sizeof(kRingTwin[0]) == kFirstSplit, "one twin per configuration");
 
 inline bool wants_bias_grad(const LaunchArgs& args) {
   for (int i = 0; i < args.n_prob; ++i)
     if (args.p[i].bias_grad) return true;
   return false;
 }
-static_assert(sizeof(kPf1Twin) / sizeof(kPf1Twin[0]) == kNumCfgs, "one twin per configuration");
+static_assert(sizeof(kPf1Twin) / sizeof(kPf1Twin[0]) == kFirstSplit, "one twin per configuration");
 
 // Whether every operand of the launch lies within 2^31 bytes of its base, as
 // the 32-bit byte offsets of the LDS-ring loop's buffer loads need.
@@ -1104,8 +1131,13 @@ inline bool ring_ok(const LaunchArgs& args, bool a_t, bool b_t) {
 // branch-free loads may not run, the two-deep twin where the interleaved or
 // ring loop would need a bias gradient, the interleaved twin where the ring's
 // offsets would not reach.
+bool split_ok(const LaunchArgs& args);  // gemm.hip
 inline int resolve_cfg(const LaunchArgs& args, bool a_t, bool b_t, int cfg) {
   if (cfg < 0 || cfg >= kNumCfgs) return cfg;
+  if (cfg >= kFirstSplit) {
+    if (split_ok(args)) return cfg;
+    cfg = cfg >= kFirstOrdered ? 0 : 20;
+  }
   if (!pf2_ok(args, a_t, b_t)) cfg = kPf1Twin[cfg];
   if (wants_bias_grad(args)) cfg = kIlTwin[cfg];
   if (!ring_ok(args, a_t, b_t)) cfg = kRingTwin[cfg];
@@ -1155,6 +1187,12 @@ void launch_any(int cfg, LaunchArgs& args, hipStream_t stream) {
   }
 }
 
+// Launchers of the plain products (gemm_plain.hip) and of the split
+// configurations (gemm_split_*.hip; mode 0, 1, 2).
+void launch_plain(bool a_t, bool b_t, int cfg, LaunchArgs& args, hipStream_t stream);
+void launch_split(int mode, bool a_t, bool b_t, int cfg, LaunchArgs& args, hipStream_t stream);
+void launch_split_nt(int mode, int cfg, LaunchArgs& args, hipStream_t stream);
+void launch_split_nn(int mode, int cfg, LaunchArgs& args, hipStream_t stream);
 // Launchers of the group modes (defined in gemm_grouped.hip): mode 1 for the
 // NN and NT layouts, mode 2 for TN.
 void launch_grouped(int mode, bool a_t, bool b_t, int cfg, LaunchArgs& args, hipStream_t stream);

@@ -223,8 +223,9 @@ inline int32_t* queue_of(void* ws, const Plan& p, int which) {
 }
 
 
+// ordered: the products take the ordered plans (GemmProblem::ordered).
 cpra_status forward_impl(const cpra_csr* g, const Plan& p, const float* params, float* Z,
-                         int64_t ldz, void* ws, hipStream_t st) {
+                         int64_t ldz, void* ws, hipStream_t st, bool ordered) {
   const int N = g->n_nodes;
   GroupRows rows{};
   if (p.G > 1) CPRA_CHECK(group_rows_build(g, static_cast<char*>(ws) + p.rows_off, &rows, st));
@@ -265,23 +266,28 @@ cpra_status forward_impl(const cpra_csr* g, const Plan& p, const float* params, 
         q.ld_add = l.out;
       }
       set_groups(p, g, &rows, 1, &q, l);
+      q.ordered = ordered;
       CPRA_CHECK(gemm_batch(false, true, &q, 1, nullptr, 0, st));
     } else {
       float* YY = fptr(ws, p.yy_off);
       const int64_t ldyy = 2 * l.out;
+      // With one weight set, Ws and Wn lie one after the other, a [2 out, in] matrix:
+      // one product reads H once.  Per-graph weights are two products (their biases
+      // are added by the self-weight one, graph g's bias on graph g's rows).
+      const int n_prob = p.G > 1 ? 2 : 1;
       GemmProblem q[2] = {};
-      for (int i = 0; i < 2; ++i) {
+      for (int i = 0; i < n_prob; ++i) {
         q[i].piece[0] = GemmPiece{H, i == 0 ? Ws : Wn, ldh, l.in, l.in};
         q[i].n_pieces = 1;
         q[i].C = YY + (i == 0 ? 0 : l.out);
         q[i].ldc = ldyy;
         q[i].M = N;
-        q[i].N = l.out;
+        q[i].N = n_prob == 1 ? 2 * l.out : l.out;
         set_groups(p, g, &rows, 1, &q[i], l);
+        q[i].ordered = ordered;
       }
-      // per-graph biases are added by the self-weight GEMM (graph g's bias on graph g's rows)
       if (p.G > 1) q[0].bias = b;
-      CPRA_CHECK(gemm_batch(false, true, q, 2, nullptr, 0, st));
+      CPRA_CHECK(gemm_batch(false, true, q, n_prob, nullptr, 0, st));
       CPRA_CHECK(aggregate(g, false, l.out, YY + l.out, ldyy, dst, ldd, YY, ldyy, p.G > 1 ? nullptr : b,
                            !last, nullptr, 0, st, P, l.out, last ? p.z_offset : nullptr, l.out,
                            queue_of(ws, p, 0)));
@@ -326,7 +332,7 @@ struct PendingReads {
 // training step's loss-term reduction, so that it needs no fork of its own.
 cpra_status backward_impl(const cpra_csr* g, const Plan& p, const float* params, const float* dZ,
                           int64_t lddz, float* grads, void* ws, hipStream_t st,
-                          SideStream* side, bool rows_ready,
+                          SideStream* side, bool rows_ready, bool ordered,
                           const std::function<cpra_status(hipStream_t)>* side_task = nullptr) {
   const int N = g->n_nodes;
   GroupRows rows{};
@@ -403,6 +409,7 @@ cpra_status backward_impl(const cpra_csr* g, const Plan& p, const float* params,
         r.mask = mask;
         r.ld_mask = ldh;
         set_groups(p, g, &rows, 1, &r, l);
+        r.ordered = ordered;
         CPRA_CHECK(before_write(dX));
         CPRA_CHECK(gemm_batch(false, false, &r, 1, nullptr, 0, st));
       }
@@ -420,6 +427,7 @@ cpra_status backward_impl(const cpra_csr* g, const Plan& p, const float* params,
         r.mask = mask;
         r.ld_mask = ldh;
         set_groups(p, g, &rows, 1, &r, l);
+        r.ordered = ordered;
         CPRA_CHECK(before_write(dX));
         return gemm_batch(false, false, &r, 1, nullptr, 0, st);
       };
@@ -439,6 +447,7 @@ cpra_status backward_impl(const cpra_csr* g, const Plan& p, const float* params,
           q[i].M = l.out;
           q[i].N = l.in;
           set_groups(p, g, &rows, 2, &q[i], l);
+          q[i].ordered = ordered;
         }
         if (p.sage) q[0].bias_grad = grads + l.off_b;  // db = dY^T 1
         return gemm_batch(true, false, q, 2, gemm_ws, p.gemm_bytes, wst);
@@ -466,6 +475,7 @@ cpra_status backward_impl(const cpra_csr* g, const Plan& p, const float* params,
           r[i].M = N;
           r[i].N = l.in;
           set_groups(p, g, &rows, 1, &r[i], l);
+          r[i].ordered = ordered;
         }
         return gemm_batch(false, false, r, 2, nullptr, 0, st);
       };
@@ -493,6 +503,7 @@ cpra_status backward_impl(const cpra_csr* g, const Plan& p, const float* params,
         q[i].M = l.out;
         q[i].N = l.in;
         set_groups(p, g, &rows, 2, &q[i], l);
+        q[i].ordered = ordered;
       }
       if (p.sage) q[0].bias_grad = grads + l.off_b;  // db = dY^T 1
       CPRA_CHECK(gemm_batch(true, false, q, 2, gemm_ws, p.gemm_bytes, wst));
@@ -564,7 +575,8 @@ cpra_status cpra_model_forward(const cpra_csr* g, const cpra_model_cfg* cfg, con
   make_plan(cfg, g, &p);
   if (ws == nullptr || ws_bytes < p.total)
     CPRA_FAIL(CPRA_ERR_WORKSPACE, "model_forward: workspace %zu < %zu bytes", ws_bytes, p.total);
-  return forward_impl(g, p, params, Z, ldz, ws, as_stream(stream));
+  // a frozen prefix that it saves feeds training steps
+  return forward_impl(g, p, params, Z, ldz, ws, as_stream(stream), cfg->train_from_layer > 0);
 }
 
 cpra_status cpra_model_backward(const cpra_csr* g, const cpra_model_cfg* cfg, const float* params,
@@ -582,7 +594,7 @@ cpra_status cpra_model_backward(const cpra_csr* g, const cpra_model_cfg* cfg, co
     CPRA_FAIL(CPRA_ERR_WORKSPACE, "model_backward: workspace %zu < %zu bytes", ws_bytes, p.total);
   SideStream* side = nullptr;
   if (overlap_enabled()) CPRA_CHECK(get_side_stream(&side));
-  CPRA_CHECK(backward_impl(g, p, params, dZ, lddz, grads, ws, as_stream(stream), side, false));
+  CPRA_CHECK(backward_impl(g, p, params, dZ, lddz, grads, ws, as_stream(stream), side, false, false));
   if (side) CPRA_CHECK(join_from(side, as_stream(stream)));
   return CPRA_OK;
 }
@@ -644,7 +656,7 @@ cpra_status cpra_train_step(const cpra_csr* g, const cpra_step_cfg* cfg, float* 
   SideStream* side = nullptr;
   if (overlap_enabled()) CPRA_CHECK(get_side_stream(&side));
   void* loss_ws = static_cast<char*>(ws) + model_bytes;
-  CPRA_CHECK(forward_impl(g, p, params, Z, S, ws, st));
+  CPRA_CHECK(forward_impl(g, p, params, Z, S, ws, st, true));
   CPRA_CHECK(loss_fwd_bwd(g, &lc, Z, S, fptr(ws, p.p_off), S, dZ, S, nullptr, loss_ws,
                           ws_bytes - model_bytes, st, terms != nullptr));
   // The step counter advances (t -> t + 1) after the loss has read t and before
@@ -667,7 +679,7 @@ cpra_status cpra_train_step(const cpra_csr* g, const cpra_step_cfg* cfg, float* 
   } else if (step_counter) {
     CPRA_CHECK(increment_counter(step_counter, st));
   }
-  CPRA_CHECK(backward_impl(g, p, params, dZ, S, grads, ws, st, side, true,
+  CPRA_CHECK(backward_impl(g, p, params, dZ, S, grads, ws, st, side, true, true,
                            side && terms ? &terms_task : nullptr));
   if (side) CPRA_CHECK(join_from(side, st));
   // only the trainable tail [first trained layer, end) when the encoder is frozen
