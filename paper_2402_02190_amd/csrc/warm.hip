@@ -10,22 +10,20 @@
 // Storage: bfloat16 activations [N, width] row-major (raw uint16 bit
 // patterns, round-to-nearest-even from float32), float32 master weights and
 // gradients, float32 output logits.  Kernels:
-//  * k_node_features -- one wavefront per node: triangle count by binary
-//    search of every neighbour's list in the node's own sorted list (integer,
+//  * k_node_features -- 16 lanes per node: triangle count by comparing every
+//    neighbour's list with the node's own (by binary search for large degrees; integer,
 //    exact), then the feature row [d/16, clustering, random channels, 0...];
-//  * k_agg_bf16 -- mean over neighbours of bf16 rows (or, transposed, the
-//    M^T gather of float32 rows with an addend and a ReLU mask), float32 sums
-//    in CSR order, bf16 result;
-//  * k_rows_mfma -- C[N, n_out] = [A_0 | A_1] B: each wavefront streams
-//    32-row tiles of A straight from memory into v_mfma_f32_32x32x16_bf16
-//    operands while B (the weights, at most 128 x 128) sits in LDS for the
-//    whole launch; bias / ReLU / bf16 or float32 store in the epilogue;
+//  * k_mpnn_layer -- one forward layer: each wavefront gathers the neighbour means of
+//    its 32 rows (float32 sums in CSR order, one rounding) into the operands of
+//    v_mfma_f32_32x32x16_bf16, next to the rows themselves, while the weights (at most
+//    128 x 128) sit in LDS; bias / ReLU / bf16 or float32 store in the epilogue;
+//  * k_rows_mfma, k_agg_t_bf16 -- the backward's dY [Ws | Wn] by 32-row tiles, and the
+//    M^T gather of its float32 rows with an addend and a ReLU mask, bf16 result;
 //  * k_wgrad_mfma -- per block of rows, the partial dY^T [X_0 | X_1] and the
 //    column sums of dY (bias gradient) through LDS-staged 64-row chunks; a
 //    second kernel adds the partials in block order (deterministic).
 #include <algorithm>
 #include <cmath>
-#include <type_traits>
 
 #include "common.hpp"
 
@@ -40,6 +38,7 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned short u16x8 __attribute__((ext_vector_type(8)));
+typedef unsigned short u16x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kMaxLayers = 8;
 constexpr int kMaxWidth = 128;    // n_out and k_total limit of the row GEMM
@@ -59,18 +58,11 @@ __device__ inline float sigmoid_of(float z) {
 }
 
 // ------------------------------------------------------------------ features
-__global__ __launch_bounds__(256) void k_node_features(int n, const int32_t* __restrict__ row_ptr,
-                                                       const int32_t* __restrict__ col_idx,
-                                                       int in_dim, int n_rand,
-                                                       const float* __restrict__ rand,
-                                                       int64_t ld_rand, uint16_t* __restrict__ feat,
-                                                       int64_t ld_feat, int64_t* __restrict__ tri) {
-  const int lane = threadIdx.x & 63;
-  const int i = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (i >= n) return;  // uniform per wavefront
-  const int b = row_ptr[i], e = row_ptr[i + 1];
-  const int d = e - b;
-  long long cnt = 0;  // sum over neighbours j of |N(i) n N(j)| = 2 T_i
+// 2 T_i by one wavefront: lanes take neighbours, each binary-searching every entry of
+// its neighbour's list in the node's own (this lane's share of the sum).
+__device__ __forceinline__ long long wedges_by_search(const int32_t* __restrict__ row_ptr,
+                                                      const int32_t* __restrict__ col_idx, int b, int e, int lane) {
+  long long cnt = 0;
   for (int k = b + lane; k < e; k += 64) {
     const int j = col_idx[k];
     const int bj = row_ptr[j], ej = row_ptr[j + 1];
@@ -84,11 +76,79 @@ __global__ __launch_bounds__(256) void k_node_features(int n, const int32_t* __r
       cnt += (lo < e && col_idx[lo] == x) ? 1 : 0;
     }
   }
+  return cnt;
+}
+
+// A wavefront takes 4 nodes, 16 lanes each.  Up to kCompareDegree neighbours a node's
+// own list sits in its lanes' registers, lane l walks the list of neighbour l (eight
+// entries in flight) and compares each entry with every own one, passed round by
+// shuffles: three dependent loads in all, where the search makes log2(d) more per
+// entry.  With a larger node among the four, they are done one after the other by
+// search (comparing costs d_i d_j, searching d_j log d_i).  N = 50,000, 5-regular:
+// 42 -> 10.7 us.
+constexpr int kCompareDegree = 32;
+__global__ __launch_bounds__(256) void k_node_features(int n, const int32_t* __restrict__ row_ptr,
+                                                       const int32_t* __restrict__ col_idx,
+                                                       int in_dim, int n_rand,
+                                                       const float* __restrict__ rand,
+                                                       int64_t ld_rand, uint16_t* __restrict__ feat,
+                                                       int64_t ld_feat, int64_t* __restrict__ tri) {
+  const int lane = threadIdx.x & 63;
+  const int sub = lane >> 4, l = lane & 15;
+  const int i0 = (blockIdx.x * 4 + (threadIdx.x >> 6)) * 4;
+  if (i0 >= n) return;  // uniform per wavefront
+  const int i = i0 + sub;
+  int b = 0, e = 0;
+  if (i < n) {
+    b = row_ptr[i];
+    e = row_ptr[i + 1];
+  }
+  const int d = e - b;
+  long long cnt = 0;  // sum over neighbours j of |N(i) n N(j)| = 2 T_i
+  if (!__any(d > kCompareDegree)) {
+    int own[2], key[2], bj[2], ej[2];  // neighbours l and l + 16
 #pragma unroll
-  for (int off = 32; off > 0; off >>= 1) cnt += __shfl_xor(cnt, off);
+    for (int h = 0; h < 2; ++h) {
+      const int t = 16 * h + l;
+      own[h] = t < d ? col_idx[b + t] : -1;
+      key[h] = t > 0 && t < d && col_idx[b + t - 1] == own[h] ? -1 : own[h];  // a repeated entry matches once
+    }
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      bj[h] = own[h] >= 0 ? row_ptr[own[h]] : 0;
+      ej[h] = own[h] >= 0 ? row_ptr[own[h] + 1] : 0;
+    }
+    int c = 0;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      for (int q = bj[h]; __any(q < ej[h]); q += 8) {
+        int x[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) x[u] = q + u < ej[h] ? col_idx[q + u] : -2;
+#pragma unroll
+        for (int p = 0; p < 2; ++p)
+          for (int t = 0; t < 16 && __any(16 * p + t < d); ++t) {
+            const int o = __shfl(key[p], t, 16);
+#pragma unroll
+            for (int u = 0; u < 8; ++u) c += x[u] == o;
+          }
+      }
+    }
+    cnt = c;
+#pragma unroll
+    for (int off = 8; off > 0; off >>= 1) cnt += __shfl_xor(cnt, off);
+  } else {
+    for (int t = 0; t < 4; ++t) {
+      long long c = wedges_by_search(row_ptr, col_idx, __shfl(b, 16 * t), __shfl(e, 16 * t), lane);
+#pragma unroll
+      for (int off = 32; off > 0; off >>= 1) c += __shfl_xor(c, off);
+      if (sub == t) cnt = c;
+    }
+  }
+  if (i >= n) return;
   const long long T = cnt / 2;
-  if (lane == 0 && tri) tri[i] = T;
-  for (int c = lane; c < in_dim; c += 64) {
+  if (l == 0 && tri) tri[i] = T;
+  for (int c = l; c < in_dim; c += 16) {
     float v = 0.0f;
     if (c == 0) {
       v = (float)d * 0.0625f;
@@ -102,11 +162,6 @@ __global__ __launch_bounds__(256) void k_node_features(int n, const int32_t* __r
 }
 
 // ------------------------------------------------------------------ casts
-__global__ void k_cast_bf16(int64_t n, const float* __restrict__ x, uint16_t* __restrict__ y) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) y[i] = f2bf(x[i]);
-}
-
 __global__ void k_zero(int64_t n, float* __restrict__ x) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) x[i] = 0.0f;
@@ -137,13 +192,13 @@ struct AggBfArgs {
   const int32_t* col_idx;
   const float* inv_deg;
   const float* col_inv_deg;  // inv_deg of each entry's column, or null (gathered instead)
-  const void* X;  // bf16 rows (forward) or float rows (transposed)
+  const float* X;
   int64_t ldx;
   uint16_t* Y;
   int64_t ldy;
-  const float* add;  // transposed only: [N, width] float addend
+  const float* add;  // [N, width] float addend
   int64_t ld_add;
-  const uint16_t* mask;  // transposed only: output zeroed where mask <= 0
+  const uint16_t* mask;  // output zeroed where mask <= 0
   int64_t ld_mask;
 };
 
@@ -159,77 +214,46 @@ __device__ inline void load8(const float* p, float* v) {
   v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
 }
 
-// Each lane owns 8 consecutive columns; the 2^lpr_log2 lanes of a row cover
-// its units = width / 8 column groups (NC groups per lane).
-template <bool TRANS, int NC>
-__global__ __launch_bounds__(256) void k_agg_bf16(AggBfArgs a) {
-  using In = typename std::conditional<TRANS, float, uint16_t>::type;
-  const In* X = static_cast<const In*>(a.X);
+// The backward's M^T dG.  Each lane owns 8 consecutive columns; the 2^lpr_log2 lanes of
+// a row cover its units = width / 8 column groups.
+__global__ __launch_bounds__(256) void k_agg_t_bf16(AggBfArgs a) {
   const int lane = threadIdx.x & 63;
   const int lpr = 1 << a.lpr_log2;
   const int sub = lane >> a.lpr_log2;
-  const int cl = lane & (lpr - 1);
+  const int u = lane & (lpr - 1);
   const int row = (blockIdx.x * 4 + (threadIdx.x >> 6)) * (64 >> a.lpr_log2) + sub;
-  if (row >= a.n) return;
-  float acc[NC][8];
+  if (row >= a.n || u >= a.units) return;
+  float acc[8];
 #pragma unroll
-  for (int c = 0; c < NC; ++c)
-#pragma unroll
-    for (int e = 0; e < 8; ++e) acc[c][e] = 0.0f;
+  for (int e = 0; e < 8; ++e) acc[e] = 0.0f;
   const int beg = a.row_ptr[row], end = a.row_ptr[row + 1];
   for (int k = beg; k < end; ++k) {
     const int j = a.col_idx[k];
-    const float s = !TRANS ? 1.0f : a.col_inv_deg ? a.col_inv_deg[k] : a.inv_deg[j];
+    const float s = a.col_inv_deg ? a.col_inv_deg[k] : a.inv_deg[j];
+    float v[8];
+    load8(a.X + (int64_t)j * a.ldx + u * 8, v);
 #pragma unroll
-    for (int c = 0; c < NC; ++c) {
-      const int u = c * lpr + cl;
-      if (u < a.units) {
-        float v[8];
-        load8(X + (int64_t)j * a.ldx + u * 8, v);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          if (TRANS) acc[c][e] += s * v[e]; else acc[c][e] += v[e];
-        }
-      }
-    }
+    for (int e = 0; e < 8; ++e) acc[e] += s * v[e];
   }
-  const float rs = TRANS ? 1.0f : a.inv_deg[row];
+  float ad[8], mk[8];
+  load8(a.add + (int64_t)row * a.ld_add + u * 8, ad);
+  load8(a.mask + (int64_t)row * a.ld_mask + u * 8, mk);
+  u16x8 w;
 #pragma unroll
-  for (int c = 0; c < NC; ++c) {
-    const int u = c * lpr + cl;
-    if (u >= a.units) continue;
-    float r[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) r[e] = TRANS ? acc[c][e] : acc[c][e] * rs;
-    if (TRANS) {
-      float ad[8], mk[8];
-      load8(a.add + (int64_t)row * a.ld_add + u * 8, ad);
-      load8(a.mask + (int64_t)row * a.ld_mask + u * 8, mk);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) r[e] = (mk[e] > 0.0f) ? r[e] + ad[e] : 0.0f;
-    }
-    u16x8 w;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) w[e] = f2bf(r[e]);
-    *reinterpret_cast<u16x8*>(a.Y + (int64_t)row * a.ldy + u * 8) = w;
-  }
+  for (int e = 0; e < 8; ++e) w[e] = f2bf(mk[e] > 0.0f ? acc[e] + ad[e] : 0.0f);
+  *reinterpret_cast<u16x8*>(a.Y + (int64_t)row * a.ldy + u * 8) = w;
 }
 
 // ------------------------------------------------------------------ row GEMM
+// The backward's dY [Ws | Wn]: C[M, n_out] = A[M, k_total] [B0 | B1].
 struct RowsArgs {
   int M, n_out, k_total;
-  const uint16_t* A[2];  // pieces along K, [M, ka[p]] with leading dimension lda[p]
-  int64_t lda[2];
-  int ka[2];
-  const uint16_t* B[2];  // b_kn = 0: [n_out, ka[p]] row-major, pieces along K
-  int nb[2];             // b_kn = 1: [k_total, nb[q]] row-major, pieces along N
-  int b_kn;
-  const float* bias;  // [n_out] or null
-  int relu;
-  uint16_t* Cb;  // bf16 output [M, n_out] (ldcb) or null
-  int64_t ldcb;
-  float* Cf;  // float output [M, n_out] (ldcf) or null
-  int64_t ldcf;
+  const uint16_t* A;
+  int64_t lda;
+  const uint16_t* B[2];  // [k_total, n_half] row-major, pieces along N
+  int n_half;
+  float* C;
+  int64_t ldc;
   int tiles;  // ceil(M / 32)
 };
 
@@ -241,17 +265,8 @@ __global__ __launch_bounds__(256) void k_rows_mfma(RowsArgs a) {
   const int kt = a.k_total;
   for (int idx = threadIdx.x; idx < NT * 32 * kt; idx += 256) {
     const int n = idx / kt, k = idx - n * kt;
-    uint16_t v;
-    if (!a.b_kn) {
-      const int p = k < a.ka[0] ? 0 : 1;
-      const int kk = p ? k - a.ka[0] : k;
-      v = a.B[p][(int64_t)n * a.ka[p] + kk];
-    } else {
-      const int q = n < a.nb[0] ? 0 : 1;
-      const int nn = q ? n - a.nb[0] : n;
-      v = a.B[q][(int64_t)k * a.nb[q] + nn];
-    }
-    Bt[n * KP + k] = v;
+    const int q = n < a.n_half ? 0 : 1;
+    Bt[n * KP + k] = a.B[q][(int64_t)k * a.n_half + (q ? n - a.n_half : n)];
   }
   __syncthreads();
 
@@ -267,10 +282,8 @@ __global__ __launch_bounds__(256) void k_rows_mfma(RowsArgs a) {
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[t][r] = 0.0f;
     for (int k0 = 0; k0 < kt; k0 += 16) {
-      const int p = k0 < a.ka[0] ? 0 : 1;
-      const int kc = (p ? k0 - a.ka[0] : k0) + 8 * g;
       u32x4 av = {0u, 0u, 0u, 0u};
-      if (row < a.M) av = *reinterpret_cast<const u32x4*>(a.A[p] + (int64_t)row * a.lda[p] + kc);
+      if (row < a.M) av = *reinterpret_cast<const u32x4*>(a.A + (int64_t)row * a.lda + k0 + 8 * g);
       const bf16x8 af = __builtin_bit_cast(bf16x8, av);
 #pragma unroll
       for (int t = 0; t < NT; ++t) {
@@ -281,20 +294,154 @@ __global__ __launch_bounds__(256) void k_rows_mfma(RowsArgs a) {
     }
     // acc[t][r] holds C[tile*32 + 8*(r/4) + 4*g + r%4][t*32 + m]
 #pragma unroll
-    for (int t = 0; t < NT; ++t) {
-      const int col = t * 32 + m;
-      const float bv = a.bias ? a.bias[col] : 0.0f;
+    for (int t = 0; t < NT; ++t)
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         const int rr = tile * 32 + 8 * (r >> 2) + 4 * g + (r & 3);
-        if (rr >= a.M) continue;
-        float v = acc[t][r] + bv;
-        if (a.relu) v = fmaxf(v, 0.0f);
-        if (a.Cb) a.Cb[(int64_t)rr * a.ldcb + col] = f2bf(v);
-        if (a.Cf) a.Cf[(int64_t)rr * a.ldcf + col] = v;
+        if (rr < a.M) a.C[(int64_t)rr * a.ldc + t * 32 + m] = acc[t][r];
       }
+  }
+}
+
+// ------------------------------------------------------------------ forward layer
+struct LayerArgs {
+  int n, tiles;
+  const int32_t* row_ptr;
+  const int32_t* col_idx;
+  const float* inv_deg;
+  const uint16_t* H;  // [n, in]
+  uint16_t* A;        // [n, in]: bf16(M H), kept for the backward
+  const float* Ws;    // float32 masters [n_out, in]
+  const float* Wn;
+  uint16_t* ws_bf;    // their bf16 shadows, written by block 0 (the backward reads them)
+  uint16_t* wn_bf;
+  const float* bias;
+  int relu;
+  uint16_t* Cb;  // bf16 output [n, n_out] or null
+  float* Cf;     // float output [n, n_out] or null
+};
+
+__device__ inline u32x4 round8(const float* v) {
+  u16x8 w;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) w[e] = f2bf(v[e]);
+  return __builtin_bit_cast(u32x4, w);
+}
+
+// Y = H bf16(Ws)^T + bf16(M H) bf16(Wn)^T + b in one launch.  A wavefront owns 32 rows;
+// lane (row, g) gathers the neighbours' columns 16 t + 8 g .. + 7 of its row straight
+// into the operand layout (FP32 sums in CSR order, four neighbours' loads in flight,
+// then the one rounding), so M H is written once for the backward and never read
+// here.  The weights are rounded from the float32 masters while they are staged, a
+// vector of 8 per load.  Rounding points and the order of every sum are those of
+// an aggregation launch followed by a product in k order, bit for bit.  Bound by the
+// chain row_ptr -> col_idx -> rows at the 1,563 wavefronts that 50,000 rows give (more
+// neighbours in flight or smaller blocks: no change).  64 -> 64 columns at N = 50,000,
+// 5-regular: 8 + 25 us in two launches (the weights staged value by value) -> 15.7 us.
+template <int NT, int KI>  // n_out / 32, in / 16
+__global__ __launch_bounds__(256) void k_mpnn_layer(LayerArgs a) {
+  constexpr int IN = 16 * KI, KT = 2 * IN, KP = KT + 8;  // LDS row pitch (bf16 elements)
+  __shared__ __attribute__((aligned(16))) uint16_t Bt[NT * 32 * KP];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int m = lane & 31, g = lane >> 5;
+  const int tile = blockIdx.x * 4 + wave;
+  const int row = tile * 32 + m;
+  const bool live = row < a.n;
+  int k = 0, end = 0;
+  if (live) {
+    k = a.row_ptr[row];
+    end = a.row_ptr[row + 1];
+  }
+  for (int v = threadIdx.x; v < NT * 32 * KT / 8; v += 256) {
+    const int n = v / (KT / 8), c = (v % (KT / 8)) * 8;
+    const bool nb = c >= IN;
+    const int at = n * IN + (nb ? c - IN : c);
+    const float* w = (nb ? a.Wn : a.Ws) + at;
+    float x[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) x[e] = w[e];
+    const u32x4 r = round8(x);
+    *reinterpret_cast<u32x4*>(&Bt[n * KP + c]) = r;
+    if (blockIdx.x == 0) *reinterpret_cast<u32x4*>((nb ? a.wn_bf : a.ws_bf) + at) = r;
+  }
+  u32x4 hv[KI], av[KI];
+#pragma unroll
+  for (int t = 0; t < KI; ++t) {
+    hv[t] = u32x4{0u, 0u, 0u, 0u};
+    if (live) hv[t] = *reinterpret_cast<const u32x4*>(a.H + (int64_t)row * IN + 16 * t + 8 * g);
+  }
+  float sum[KI][8];
+#pragma unroll
+  for (int t = 0; t < KI; ++t)
+#pragma unroll
+    for (int e = 0; e < 8; ++e) sum[t][e] = 0.0f;
+  constexpr int CH = 4;
+  for (; k < end; k += CH) {
+    int j[CH];
+    u32x4 x[CH][KI];
+#pragma unroll
+    for (int c = 0; c < CH; ++c) j[c] = a.col_idx[min(k + c, end - 1)];
+#pragma unroll
+    for (int c = 0; c < CH; ++c)
+#pragma unroll
+      for (int t = 0; t < KI; ++t) {
+        x[c][t] = u32x4{0u, 0u, 0u, 0u};  // past the row's end: adds an exact zero (sums never hold -0)
+        if (k + c < end) x[c][t] = *reinterpret_cast<const u32x4*>(a.H + (int64_t)j[c] * IN + 16 * t + 8 * g);
+      }
+#pragma unroll
+    for (int c = 0; c < CH; ++c)
+#pragma unroll
+      for (int t = 0; t < KI; ++t) {
+        const u16x8 y = __builtin_bit_cast(u16x8, x[c][t]);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) sum[t][e] += bf2f(y[e]);
+      }
+  }
+  const float rs = live ? a.inv_deg[row] : 0.0f;
+#pragma unroll
+  for (int t = 0; t < KI; ++t) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) sum[t][e] *= rs;
+    av[t] = round8(sum[t]);
+    if (live) *reinterpret_cast<u32x4*>(a.A + (int64_t)row * IN + 16 * t + 8 * g) = av[t];
+  }
+  __syncthreads();
+  if (tile >= a.tiles) return;
+  // The weights are the first operand, so that a lane ends with columns of its own row:
+  // acc[t][4 q + e] holds C[row][t * 32 + 8 q + 4 g + e].
+  f32x16 acc[NT];
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[t][r] = 0.0f;
+#pragma unroll
+  for (int q = 0; q < 2 * KI; ++q) {
+    const bf16x8 af = __builtin_bit_cast(bf16x8, q < KI ? hv[q % KI] : av[q % KI]);
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      const u32x4 bv = *reinterpret_cast<const u32x4*>(&Bt[(t * 32 + m) * KP + 16 * q + 8 * g]);
+      acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, bv), af, acc[t], 0, 0, 0);
     }
   }
+  if (!live) return;
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int col = t * 32 + 8 * q + 4 * g;
+      float v[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        v[e] = acc[t][4 * q + e] + a.bias[col + e];
+        if (a.relu) v[e] = fmaxf(v[e], 0.0f);
+      }
+      if (a.Cb) {
+        uint16_t* o = a.Cb + (int64_t)row * (NT * 32) + col;
+        const u16x4 y = {f2bf(v[0]), f2bf(v[1]), f2bf(v[2]), f2bf(v[3])};
+        *reinterpret_cast<u16x4*>(o) = y;
+      }
+      if (a.Cf) __builtin_memcpy(a.Cf + (int64_t)row * (NT * 32) + col, v, sizeof v);
+    }
 }
 
 // ------------------------------------------------------------------ weight gradient
@@ -485,24 +632,19 @@ inline T* at(void* ws, size_t off) {
   return reinterpret_cast<T*>(static_cast<char*>(ws) + off);
 }
 
-cpra_status agg_bf16(const cpra_csr* g, bool trans, int width, const void* X, int64_t ldx,
-                     uint16_t* Y, int64_t ldy, const float* add, int64_t ld_add,
-                     const uint16_t* mask, int64_t ld_mask, hipStream_t st) {
+cpra_status agg_t_bf16(const cpra_csr* g, int width, const float* X, int64_t ldx, uint16_t* Y,
+                       int64_t ldy, const float* add, int64_t ld_add, const uint16_t* mask,
+                       int64_t ld_mask, hipStream_t st) {
   const int units = width / 8;
-  int lpr = 1;
-  while (lpr < units) lpr <<= 1;
   int lpr_log2 = 0;
-  while ((1 << lpr_log2) < lpr) ++lpr_log2;
+  while ((1 << lpr_log2) < units) ++lpr_log2;
   AggBfArgs a{g->n_nodes, units, lpr_log2, g->row_ptr, g->col_idx, g->inv_deg, g->col_inv_deg,
               X, ldx, Y, ldy, add, ld_add, mask, ld_mask};
   const int rows_per_block = 4 * (64 >> lpr_log2);
   const int blocks = (int)ceil_div(g->n_nodes, rows_per_block);
-  const double in_b = trans ? 4.0 : 2.0;
-  const double bytes = (double)g->n_nodes * width * (in_b + 2.0 + (trans ? 6.0 : 0.0)) +
-                       4.0 * (double)g->nnz + 8.0 * g->n_nodes;
-  ProfScope ps(trans ? "mpnn_aggregate_transposed" : "mpnn_aggregate", st, 0.0, bytes);
-  if (trans) hipLaunchKernelGGL((k_agg_bf16<true, 1>), dim3(blocks), dim3(256), 0, st, a);
-  else hipLaunchKernelGGL((k_agg_bf16<false, 1>), dim3(blocks), dim3(256), 0, st, a);
+  const double bytes = (double)g->n_nodes * width * 12.0 + 4.0 * (double)g->nnz + 8.0 * g->n_nodes;
+  ProfScope ps("mpnn_aggregate_transposed", st, 0.0, bytes);
+  hipLaunchKernelGGL(k_agg_t_bf16, dim3(blocks), dim3(256), 0, st, a);
   CPRA_CHECK_LAUNCH("mpnn aggregate");
   return CPRA_OK;
 }
@@ -513,8 +655,7 @@ cpra_status rows_gemm(const RowsArgs& a0, hipStream_t st) {
   if (a.M == 0) return CPRA_OK;
   const int blocks = (int)std::min<int64_t>(ceil_div(a.tiles, 4), 2048);
   const double flops = 2.0 * a.M * (double)a.n_out * a.k_total;
-  const double bytes = (double)a.M * (2.0 * a.k_total + (a.Cb ? 2.0 : 0.0) * a.n_out +
-                                      (a.Cf ? 4.0 : 0.0) * a.n_out);
+  const double bytes = (double)a.M * (2.0 * a.k_total + 4.0 * a.n_out);
   ProfScope ps("mpnn_gemm_bf16", st, flops, bytes);
   switch (a.n_out / 32) {
     case 1: hipLaunchKernelGGL((k_rows_mfma<1>), dim3(blocks), dim3(256), 0, st, a); break;
@@ -568,42 +709,53 @@ cpra_status wgrad(const MPlan& p, int k, const uint16_t* dY, const uint16_t* H, 
   return CPRA_OK;
 }
 
+template <int NT>
+cpra_status launch_layer(int ki, const LayerArgs& a, dim3 grid, hipStream_t st) {
+  switch (ki) {
+    case 1: hipLaunchKernelGGL((k_mpnn_layer<NT, 1>), grid, dim3(256), 0, st, a); break;
+    case 2: hipLaunchKernelGGL((k_mpnn_layer<NT, 2>), grid, dim3(256), 0, st, a); break;
+    case 3: hipLaunchKernelGGL((k_mpnn_layer<NT, 3>), grid, dim3(256), 0, st, a); break;
+    case 4: hipLaunchKernelGGL((k_mpnn_layer<NT, 4>), grid, dim3(256), 0, st, a); break;
+    default: CPRA_FAIL(CPRA_ERR_SHAPE, "mpnn layer: in %d", 16 * ki);
+  }
+  CPRA_CHECK_LAUNCH("mpnn layer");
+  return CPRA_OK;
+}
+
 cpra_status mpnn_forward_impl(const cpra_csr* g, const MPlan& p, const float* params,
                               const uint16_t* feat, float* Zw, void* ws, hipStream_t st) {
   uint16_t* wbf = at<uint16_t>(ws, p.wbf_off);
-  {
-    ProfScope ps("mpnn_cast", st, 0.0, 6.0 * (double)p.n_params);
-    hipLaunchKernelGGL(k_cast_bf16, dim3((unsigned)ceil_div(p.n_params, 256)), dim3(256), 0, st,
-                       p.n_params, params, wbf);
-    CPRA_CHECK_LAUNCH("mpnn cast");
-  }
   const uint16_t* H = feat;
   for (int k = 0; k < p.L; ++k) {
     const MLayer& l = p.layer[k];
     const bool last = k == p.L - 1;
-    uint16_t* A = at<uint16_t>(ws, p.a_off[k]);
-    CPRA_CHECK(agg_bf16(g, false, l.in, H, l.in, A, l.in, nullptr, 0, nullptr, 0, st));
-    RowsArgs r{};
-    r.M = p.N;
-    r.n_out = l.out;
-    r.k_total = 2 * l.in;
-    r.A[0] = H;
-    r.A[1] = A;
-    r.lda[0] = r.lda[1] = l.in;
-    r.ka[0] = r.ka[1] = l.in;
-    r.B[0] = wbf + l.off_ws;
-    r.B[1] = wbf + l.off_wn;
-    r.b_kn = 0;
-    r.bias = params + l.off_b;
-    r.relu = last ? 0 : 1;
-    if (last) {
-      r.Cf = Zw;
-      r.ldcf = l.out;
-    } else {
-      r.Cb = at<uint16_t>(ws, p.h_off[k + 1]);
-      r.ldcb = l.out;
+    LayerArgs a{};
+    a.n = p.N;
+    a.tiles = (int)ceil_div(p.N, 32);
+    a.row_ptr = g->row_ptr;
+    a.col_idx = g->col_idx;
+    a.inv_deg = g->inv_deg;
+    a.H = H;
+    a.A = at<uint16_t>(ws, p.a_off[k]);
+    a.Ws = params + l.off_ws;
+    a.Wn = params + l.off_wn;
+    a.ws_bf = wbf + l.off_ws;
+    a.wn_bf = wbf + l.off_wn;
+    a.bias = params + l.off_b;
+    a.relu = last ? 0 : 1;
+    if (last) a.Cf = Zw; else a.Cb = at<uint16_t>(ws, p.h_off[k + 1]);
+    const double n = p.N;
+    ProfScope ps("mpnn_layer_bf16", st, 4.0 * n * l.out * l.in,
+                 n * (4.0 * l.in + (last ? 4.0 : 2.0) * l.out) + 4.0 * (double)g->nnz + 8.0 * n,
+                 2.0 * (double)g->nnz * l.in);
+    const dim3 grid((unsigned)ceil_div(a.tiles, 4));
+    switch (l.out / 32) {
+      case 1: CPRA_CHECK(launch_layer<1>(l.in / 16, a, grid, st)); break;
+      case 2: CPRA_CHECK(launch_layer<2>(l.in / 16, a, grid, st)); break;
+      case 3: CPRA_CHECK(launch_layer<3>(l.in / 16, a, grid, st)); break;
+      case 4: CPRA_CHECK(launch_layer<4>(l.in / 16, a, grid, st)); break;
+      default: CPRA_FAIL(CPRA_ERR_SHAPE, "mpnn layer: n_out %d", l.out);
     }
-    CPRA_CHECK(rows_gemm(r, st));
     if (!last) H = at<uint16_t>(ws, p.h_off[k + 1]);
   }
   return CPRA_OK;
@@ -632,19 +784,16 @@ cpra_status mpnn_backward_impl(const cpra_csr* g, const MPlan& p, const uint16_t
     r.M = p.N;
     r.n_out = 2 * l.in;
     r.k_total = l.out;
-    r.A[0] = r.A[1] = dY;
-    r.lda[0] = r.lda[1] = l.out;
-    r.ka[0] = l.out;
-    r.ka[1] = 0;
+    r.A = dY;
+    r.lda = l.out;
     r.B[0] = wbf + l.off_ws;
     r.B[1] = wbf + l.off_wn;
-    r.nb[0] = r.nb[1] = l.in;
-    r.b_kn = 1;
-    r.Cf = G;
-    r.ldcf = 2 * l.in;
+    r.n_half = l.in;
+    r.C = G;
+    r.ldc = 2 * l.in;
     CPRA_CHECK(rows_gemm(r, st));
     uint16_t* dYn = at<uint16_t>(ws, p.dy_off[cur ^ 1]);
-    CPRA_CHECK(agg_bf16(g, true, l.in, G + l.in, 2 * l.in, dYn, l.in, G, 2 * l.in, H, l.in, st));
+    CPRA_CHECK(agg_t_bf16(g, l.in, G + l.in, 2 * l.in, dYn, l.in, G, 2 * l.in, H, l.in, st));
     dY = dYn;
     cur ^= 1;
   }
@@ -679,7 +828,7 @@ cpra_status cpra_node_features(const cpra_csr* g, int32_t in_dim, int32_t n_rand
                        (triangles ? 8.0 : 0.0) * g->n_nodes + 4.0 * (double)g->nnz +
                        4.0 * (g->n_nodes + 1.0);
   ProfScope ps("node_features", st, 0.0, bytes);
-  hipLaunchKernelGGL(k_node_features, dim3((unsigned)ceil_div(g->n_nodes, 4)), dim3(256), 0, st,
+  hipLaunchKernelGGL(k_node_features, dim3((unsigned)ceil_div(g->n_nodes, 16)), dim3(256), 0, st,
                      g->n_nodes, g->row_ptr, g->col_idx, in_dim, n_rand, rand, ld_rand, feat,
                      ld_feat, triangles);
   CPRA_CHECK_LAUNCH("node_features");
