@@ -2,12 +2,12 @@
 // Aggregate step with the 1/|N(v)| normalisation).
 //
 // Layout: a 64-lane wavefront holds 64/LPR rows; the LPR lanes of one row
-// cover its columns in VEC-float vectors, NC vectors per lane.  Each lane
-// walks its row's neighbour list in chunks (the index loads are uniform across
-// the row's lanes) and issues a chunk's row gathers together; every gathered
-// row segment is read as contiguous, coalesced vectors.  Sums run in CSR
-// order, so results are deterministic.
+// cover its columns in VEC-float vectors, NC vectors per lane.  A row's
+// neighbour list is walked in chunks, a chunk's row gathers issued together;
+// every gathered row segment is read as contiguous, coalesced vectors.  Sums
+// run in CSR order, so results are deterministic.
 #include <algorithm>
+#include <type_traits>
 
 #include "common.hpp"
 
@@ -23,7 +23,6 @@ struct Vec<1> {
   __device__ static T zero() { return 0.0f; }
   __device__ static void axpy(T& acc, float s, const T& x) { acc += s * x; }
   __device__ static void add(T& acc, const T& x) { acc += x; }
-  __device__ static void scale(T& acc, float s) { acc *= s; }
 };
 template <>
 struct Vec<2> {
@@ -31,7 +30,6 @@ struct Vec<2> {
   __device__ static T zero() { return make_float2(0.f, 0.f); }
   __device__ static void axpy(T& acc, float s, const T& x) { acc.x += s * x.x; acc.y += s * x.y; }
   __device__ static void add(T& acc, const T& x) { acc.x += x.x; acc.y += x.y; }
-  __device__ static void scale(T& acc, float s) { acc.x *= s; acc.y *= s; }
 };
 template <>
 struct Vec<4> {
@@ -43,7 +41,6 @@ struct Vec<4> {
   __device__ static void add(T& acc, const T& x) {
     acc.x += x.x; acc.y += x.y; acc.z += x.z; acc.w += x.w;
   }
-  __device__ static void scale(T& acc, float s) { acc.x *= s; acc.y *= s; acc.z *= s; acc.w *= s; }
 };
 
 template <int VEC>
@@ -57,6 +54,14 @@ __device__ inline void set_comp(typename Vec<VEC>::T& v, int e, float x) {
   if constexpr (VEC == 1) v = x;
   else if constexpr (VEC == 2) { if (e == 0) v.x = x; else v.y = x; }
   else { if (e == 0) v.x = x; else if (e == 1) v.y = x; else if (e == 2) v.z = x; else v.w = x; }
+}
+
+// The mean's factor, rounded by itself (never fused with the addend that follows).
+template <int VEC>
+__device__ inline void scale(typename Vec<VEC>::T& v, float s) {
+#pragma clang fp contract(off)
+#pragma unroll
+  for (int e = 0; e < VEC; ++e) set_comp<VEC>(v, e, comp<VEC>(v, e) * s);
 }
 
 constexpr double kStreamOutBytes = 32.0 * 1024 * 1024;
@@ -83,6 +88,7 @@ struct AggArgs {
   int64_t ld_sig;
   const float* add2;  // optional second addend [N, width] (ld_add2)
   int64_t ld_add2;
+  unsigned nnz_bytes;  // of col_idx, where that fits
   int32_t* queue;  // persistent launches: the work queue (kQueueInts counters)
   int units;       // persistent launches: row blocks of 4 wavefronts
   int chunk;       // persistent launches: row blocks per dequeue
@@ -109,15 +115,30 @@ __device__ inline void store_nt(const typename Vec<VEC>::T& v, float* p) {
 
 __device__ inline float sigmoid_of(float z) {
   const float e = expf(-fabsf(z));
-  const float r = 1.0f / (1.0f + e);
+  const float r = recip_1_2(1.0f + e);
   return z >= 0.0f ? r : e * r;
 }
 
 // Row block `unit` (4 wavefronts of 64/LPR rows each).
-template <int VEC, int NC, bool TRANS>
+//
+// A row's entries go in chunks of CH, all gathers of a chunk in flight; the adds run in
+// CSR order.  With one vector per lane each lane loads one of the chunk's entries and
+// the row's others receive it by a permute.  Entries past the row's end are not gathered
+// and add an exact zero (the sums never hold -0, so x + 0 = x).
+//
+// On sparse graphs the instructions bound it as much as memory does: with 64-bit
+// addresses a gather spent about 60 cycles on multiplies for 16 of loading, every lane
+// loaded every entry, and a chunk of the transposed gather waited for its entries before
+// it asked for their factors.  NARROW (every operand below 4 GiB, n and the row strides
+// in bytes below 2^24): one 24-bit multiply-add per gather, entries and factors loaded
+// together.  252 graphs of 2,750 nodes, mean degree 7, 32 columns: 129 -> 113 us, and
+// transposed 79 -> 73 us.  On one large 20-regular graph the L2 misses bound it
+// (100,000 x 128: 137 -> 133 us, 7.7 TB/s of rows).
+template <int VEC, int NC, bool TRANS, bool NARROW, int CH>
 __device__ __forceinline__ void agg_unit(const AggArgs& a, int unit) {
   using V = typename Vec<VEC>::T;
   using O = Vec<VEC>;
+  constexpr bool kEarly = !TRANS && NC <= 2;  // addends and mask in flight along with the gathers
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
   const int lpr = 1 << a.lpr_log2;
@@ -125,89 +146,138 @@ __device__ __forceinline__ void agg_unit(const AggArgs& a, int unit) {
   const int cl = lane & (lpr - 1);
   const int rpw = 64 >> a.lpr_log2;
   const int row = (unit * 4 + wave) * rpw + sub;
-  if (row >= a.n) return;
   const int units = a.width / VEC;
+  const bool spread = NC == 1 && lpr >= CH;  // uniform
+  const int first = (lane & ~(lpr - 1)) << 2;
 
-  V acc[NC];
+  int k = 0, end = 0;
+  if (row < a.n) {
+    k = a.row_ptr[row];
+    end = a.row_ptr[row + 1];
+  }
+  // Entry `at` of the CSR arrays and its factor (0 past the row's end).
+  const unsigned nnz_b = NARROW ? a.nnz_bytes : 0;
+  const __amdgpu_buffer_rsrc_t J = __builtin_amdgcn_make_buffer_rsrc((void*)a.col_idx, (short)0, nnz_b, 0x00020000);
+  const __amdgpu_buffer_rsrc_t W = __builtin_amdgcn_make_buffer_rsrc((void*)a.col_inv_deg, (short)0, nnz_b, 0x00020000);
+  auto entry = [&](int at, int* j, float* s) {
+    const bool in = at < end;
+    if constexpr (NARROW) {
+      const unsigned off = in ? (unsigned)at * 4u : ~0u;  // past the buffer: reads as 0
+      *j = (int)__builtin_amdgcn_raw_buffer_load_b32(J, off, 0, 0);
+      if (TRANS) {
+        if (a.col_inv_deg) *s = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(W, off, 0, 0));
+        else *s = in ? a.inv_deg[*j] : 0.f;
+      }
+    } else {
+      *j = 0;
+      *s = 0.f;
+      if (!in) return;
+      *j = a.stream_out ? __builtin_nontemporal_load(a.col_idx + at) : a.col_idx[at];
+      if (TRANS) *s = a.col_inv_deg ? a.col_inv_deg[at] : a.inv_deg[*j];
+    }
+  };
+
+  // element u of row `row` of an operand of leading dimension ld
+  auto at = [&](auto* p, int64_t ld, int u) {
+    using P = decltype(p);
+    using C = typename std::conditional<std::is_const<std::remove_pointer_t<P>>::value, const char, char>::type;
+    if constexpr (NARROW)
+      return reinterpret_cast<P>(reinterpret_cast<C*>(p) +
+                                 (__umul24((unsigned)row, (unsigned)ld * 4u) + (unsigned)u * (VEC * 4u)));
+    else
+      return p + (int64_t)row * ld + u * VEC;
+  };
+  V acc[NC], ad[NC], ad2[NC], mk[NC];
+  auto extras = [&](int c, int u) {
+    if (a.add) ad[c] = *reinterpret_cast<const V*>(at(a.add, a.ld_add, u));
+    if (a.add2) ad2[c] = *reinterpret_cast<const V*>(at(a.add2, a.ld_add2, u));
+    if (a.mask) mk[c] = *reinterpret_cast<const V*>(at(a.mask, a.ld_mask, u));
+  };
+  unsigned col[NC];  // byte offset of the lane's vectors in a row (past the width: the last one again)
+  float rs = 1.f;
 #pragma unroll
-  for (int c = 0; c < NC; ++c) acc[c] = O::zero();
+  for (int c = 0; c < NC; ++c) {
+    acc[c] = ad[c] = ad2[c] = mk[c] = O::zero();
+    const int u = c * lpr + cl;
+    col[c] = (unsigned)min(u, units - 1) * (VEC * 4u);
+    if (kEarly && row < a.n && u < units) extras(c, u);
+  }
+  if (!TRANS && row < a.n) rs = a.inv_deg[row];
 
-  // Neighbours in chunks of CH (all index loads, then all row gathers, then
-  // the adds in CSR order); the entries of a last partial chunk past the
-  // row's end are not gathered and add an exact zero instead (the sums never
-  // hold -0, so x + 0 = x), so a row costs two dependent round trips per
-  // chunk and there is no serial tail.
-  constexpr int CH = NC <= 2 ? 8 : 4;
-  const int beg = a.row_ptr[row];
-  const int end = a.row_ptr[row + 1];
-  for (int k = beg; k < end; k += CH) {
-    const int n_in = min(CH, end - k);
+  const unsigned ldb = (unsigned)a.ldx * 4u;
+  for (; k < end; k += CH) {
     int j[CH];
     float s[CH];
+    if (spread) {
+      int jl;
+      float sl;
+      entry(k + (cl & (CH - 1)), &jl, &sl);
 #pragma unroll
-    for (int i = 0; i < CH; ++i)
-      j[i] = a.stream_out ? __builtin_nontemporal_load(a.col_idx + min(k + i, end - 1))
-                          : a.col_idx[min(k + i, end - 1)];
+      for (int i = 0; i < CH; ++i) {
+        j[i] = __builtin_amdgcn_ds_bpermute(first + 4 * i, jl);
+        if (TRANS) s[i] = __int_as_float(__builtin_amdgcn_ds_bpermute(first + 4 * i, __float_as_int(sl)));
+      }
+    } else {
 #pragma unroll
-    for (int i = 0; i < CH; ++i)
-      s[i] = !TRANS ? 1.f
-                    : a.col_inv_deg ? a.col_inv_deg[min(k + i, end - 1)] : a.inv_deg[j[i]];
+      for (int i = 0; i < CH; ++i) entry(k + i, &j[i], &s[i]);
+    }
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
-      const int u = c * lpr + cl;
-      if (u < units) {
-        V x[CH];
+      V x[CH];
 #pragma unroll
-        for (int i = 0; i < CH; ++i)  // padded entries are not gathered
-          x[i] = i < n_in ? *reinterpret_cast<const V*>(a.X + (int64_t)j[i] * a.ldx + u * VEC)
-                          : O::zero();
-#pragma unroll
-        for (int i = 0; i < CH; ++i) {  // and add an exact zero (no branch between the adds)
-          if constexpr (TRANS) O::axpy(acc[c], s[i], x[i]); else O::add(acc[c], x[i]);
+      for (int i = 0; i < CH; ++i) {
+        x[i] = O::zero();
+        if (k + i < end) {
+          const char* r = NARROW ? reinterpret_cast<const char*>(a.X) + (__umul24((unsigned)j[i], ldb) + col[c])
+                                 : reinterpret_cast<const char*>(a.X + (int64_t)j[i] * a.ldx) + col[c];
+          x[i] = *reinterpret_cast<const V*>(r);
         }
+      }
+#pragma unroll
+      for (int i = 0; i < CH; ++i) {
+        if constexpr (TRANS) O::axpy(acc[c], s[i], x[i]); else O::add(acc[c], x[i]);
       }
     }
   }
-  const float rs = TRANS ? 1.f : a.inv_deg[row];
+  if (row >= a.n) return;
 #pragma unroll
   for (int c = 0; c < NC; ++c) {
     const int u = c * lpr + cl;
     if (u >= units) continue;
+    if (!kEarly) extras(c, u);
     V r = acc[c];
-    if constexpr (!TRANS) O::scale(r, rs);
-    if (a.add) O::add(r, *reinterpret_cast<const V*>(a.add + (int64_t)row * a.ld_add + u * VEC));
-    if (a.add2) O::add(r, *reinterpret_cast<const V*>(a.add2 + (int64_t)row * a.ld_add2 + u * VEC));
+    if constexpr (!TRANS) scale<VEC>(r, rs);
+    if (a.add) O::add(r, ad[c]);
+    if (a.add2) O::add(r, ad2[c]);
     if (a.bias) O::add(r, *reinterpret_cast<const V*>(a.bias + u * VEC));
     if (a.relu || a.mask) {
-      V mk = O::zero();
-      if (a.mask) mk = *reinterpret_cast<const V*>(a.mask + (int64_t)row * a.ld_mask + u * VEC);
 #pragma unroll
       for (int e = 0; e < VEC; ++e) {
         float x = comp<VEC>(r, e);
         if (a.relu) x = fmaxf(x, 0.0f);
-        if (a.mask && !(comp<VEC>(mk, e) > 0.0f)) x = 0.0f;
+        if (a.mask && !(comp<VEC>(mk[c], e) > 0.0f)) x = 0.0f;
         set_comp<VEC>(r, e, x);
       }
     }
-    if (a.stream_out) store_nt<VEC>(r, a.Y + (int64_t)row * a.ldy + u * VEC);
-    else *reinterpret_cast<V*>(a.Y + (int64_t)row * a.ldy + u * VEC) = r;
+    if (a.stream_out) store_nt<VEC>(r, at(a.Y, a.ldy, u));
+    else *reinterpret_cast<V*>(at(a.Y, a.ldy, u)) = r;
     if (a.sig_out) {
       V sg;
 #pragma unroll
       for (int e = 0; e < VEC; ++e) set_comp<VEC>(sg, e, sigmoid_of(comp<VEC>(r, e)));
-      *reinterpret_cast<V*>(a.sig_out + (int64_t)row * a.ld_sig + u * VEC) = sg;
+      *reinterpret_cast<V*>(at(a.sig_out, a.ld_sig, u)) = sg;
     }
   }
 }
 
 // One block per row block, in XCD order.
-template <int VEC, int NC, bool TRANS>
+template <int VEC, int NC, bool TRANS, bool NARROW, int CH>
 __global__ __launch_bounds__(256) void k_aggregate(AggArgs a) {
-  agg_unit<VEC, NC, TRANS>(a, xcd_unit(blockIdx.x, gridDim.x));
+  agg_unit<VEC, NC, TRANS, NARROW, CH>(a, xcd_unit(blockIdx.x, gridDim.x));
 }
 
 // Persistent: at most the resident blocks, each taking row blocks from the queue.
-template <int VEC, int NC, bool TRANS>
+template <int VEC, int NC, bool TRANS, bool NARROW, int CH>
 __global__ __launch_bounds__(256) void k_aggregate_persistent(AggArgs a) {
   __shared__ int s_chunk;
   const int chunks = (a.units + a.chunk - 1) / a.chunk;
@@ -217,7 +287,7 @@ __global__ __launch_bounds__(256) void k_aggregate_persistent(AggArgs a) {
     const int c = s_chunk;
     if (c < 0) break;  // uniform across the block
     const int u1 = min(a.units, (c + 1) * a.chunk);
-    for (int u = c * a.chunk; u < u1; ++u) agg_unit<VEC, NC, TRANS>(a, u);
+    for (int u = c * a.chunk; u < u1; ++u) agg_unit<VEC, NC, TRANS, NARROW, CH>(a, u);
     __syncthreads();  // s_chunk is rewritten by the next dequeue
   }
 }
@@ -226,7 +296,7 @@ inline bool aligned(const void* p, int bytes) {
   return p == nullptr || (reinterpret_cast<uintptr_t>(p) % bytes) == 0;
 }
 
-template <int VEC, bool TRANS>
+template <int VEC, bool TRANS, bool NARROW>
 cpra_status launch_nc(const AggArgs& a, int nc, int blocks, hipStream_t stream, int64_t nnz) {
   // compulsory bytes: X once, Y written, add/mask read, CSR, inv_deg
   const double nw = (double)a.n * a.width * 4.0;
@@ -237,32 +307,54 @@ cpra_status launch_nc(const AggArgs& a, int nc, int blocks, hipStream_t stream, 
   ProfScope ps(TRANS ? "aggregate_transposed" : "aggregate", stream, 0.0, bytes,
                4.0 * (double)nnz * a.width);
   if (a.queue) CPRA_CHECK(zero_queue(a.queue, stream));
+  auto launch = [&](auto nc_, auto ch_) {
+    constexpr int NCV = decltype(nc_)::value, CHV = decltype(ch_)::value;
+    if (a.queue) {
+      const int cap = resident_blocks(
+          reinterpret_cast<const void*>(&k_aggregate_persistent<VEC, NCV, TRANS, NARROW, CHV>), 256);
+      AggArgs ap = a;
+      const int grid = std::min(a.units, cap);
+      ap.chunk = queue_chunk(a.units, grid);
+      hipLaunchKernelGGL((k_aggregate_persistent<VEC, NCV, TRANS, NARROW, CHV>), dim3(grid), dim3(256), 0, stream,
+                         ap);
+    } else {
+      hipLaunchKernelGGL((k_aggregate<VEC, NCV, TRANS, NARROW, CHV>), dim3(blocks), dim3(256), 0, stream, a);
+    }
+  };
+  // Chunks of 8 entries (of 4 for four vectors and more per lane, for the registers).
+  // With two vectors per lane and a table of twice an XCD's L2 and more, 8 gathers per
+  // lane in flight only push each other's lines out: 20-regular, 100,000 x 32: 44 us
+  // with chunks of 8 and 33 with chunks of 2 (transposed 45 and 42), 10,000 x 256: 20.6
+  // and 17.4.  Below, the latency counts: 10,000 x 128: 10.2 and 11.7, 2,000 x 64: 4.9
+  // and 5.6.
+  const bool misses = (double)a.n * a.ldx * 4.0 > 8.0 * 1024 * 1024;
   switch (nc) {
-#define CPRA_AGG_CASE(NCV)                                                                     \
-  case NCV:                                                                                    \
-    if (a.queue) {                                                                             \
-      const int cap = resident_blocks(reinterpret_cast<const void*>(                           \
-                                          &k_aggregate_persistent<VEC, NCV, TRANS>), 256);     \
-      AggArgs ap = a;                                                                          \
-      const int grid = std::min(a.units, cap);                                                 \
-      ap.chunk = queue_chunk(a.units, grid);                                                   \
-      hipLaunchKernelGGL((k_aggregate_persistent<VEC, NCV, TRANS>), dim3(grid), dim3(256), 0,  \
-                         stream, ap);                                                          \
-    } else {                                                                                   \
-      hipLaunchKernelGGL((k_aggregate<VEC, NCV, TRANS>), dim3(blocks), dim3(256), 0, stream, a); \
-    }                                                                                          \
-    break;
-    CPRA_AGG_CASE(1)
-    CPRA_AGG_CASE(2)
-    CPRA_AGG_CASE(4)
-    CPRA_AGG_CASE(8)
-    CPRA_AGG_CASE(16)
-#undef CPRA_AGG_CASE
+    case 1: launch(std::integral_constant<int, 1>{}, std::integral_constant<int, 8>{}); break;
+    case 2:
+      if (misses) launch(std::integral_constant<int, 2>{}, std::integral_constant<int, 2>{});
+      else launch(std::integral_constant<int, 2>{}, std::integral_constant<int, 8>{});
+      break;
+    case 4: launch(std::integral_constant<int, 4>{}, std::integral_constant<int, 4>{}); break;
+    case 8: launch(std::integral_constant<int, 8>{}, std::integral_constant<int, 4>{}); break;
+    case 16: launch(std::integral_constant<int, 16>{}, std::integral_constant<int, 4>{}); break;
     default:
       CPRA_FAIL(CPRA_ERR_SHAPE, "aggregate: width too large");
   }
   CPRA_CHECK_LAUNCH("aggregate");
   return CPRA_OK;
+}
+
+template <bool NARROW>
+cpra_status launch_vec(const AggArgs& a, bool transpose, int vec, int nc, int blocks, hipStream_t stream,
+                       int64_t nnz) {
+  if (transpose) {
+    if (vec == 4) return launch_nc<4, true, NARROW>(a, nc, blocks, stream, nnz);
+    if (vec == 2) return launch_nc<2, true, NARROW>(a, nc, blocks, stream, nnz);
+    return launch_nc<1, true, NARROW>(a, nc, blocks, stream, nnz);
+  }
+  if (vec == 4) return launch_nc<4, false, NARROW>(a, nc, blocks, stream, nnz);
+  if (vec == 2) return launch_nc<2, false, NARROW>(a, nc, blocks, stream, nnz);
+  return launch_nc<1, false, NARROW>(a, nc, blocks, stream, nnz);
 }
 
 }  // namespace
@@ -304,16 +396,14 @@ cpra_status aggregate(const cpra_csr* g, bool transpose, int width, const float*
   int blocks = (int)xcd_grid(units_rb);
   AggArgs a{g->n_nodes, width, lpr_log2, relu ? 1 : 0, g->row_ptr, g->col_idx, g->inv_deg,
             g->col_inv_deg, X, ldx, Y, ldy, add, ld_add, bias, mask, ld_mask, sig_out, ld_sig, add2, ld_add2,
-            (queue && persistent_enabled()) ? queue : nullptr, units_rb, 1,
+            (unsigned)(g->nnz * 4), (queue && persistent_enabled()) ? queue : nullptr, units_rb, 1,
             (double)g->n_nodes * width * 4.0 > kStreamOutBytes ? 1 : 0};
-  if (transpose) {
-    if (vec == 4) return launch_nc<4, true>(a, nc, blocks, stream, g->nnz);
-    if (vec == 2) return launch_nc<2, true>(a, nc, blocks, stream, g->nnz);
-    return launch_nc<1, true>(a, nc, blocks, stream, g->nnz);
-  }
-  if (vec == 4) return launch_nc<4, false>(a, nc, blocks, stream, g->nnz);
-  if (vec == 2) return launch_nc<2, false>(a, nc, blocks, stream, g->nnz);
-  return launch_nc<1, false>(a, nc, blocks, stream, g->nnz);
+  // 32-bit byte offsets where every one fits, from 24-bit factors.
+  bool narrow = g->n_nodes < (1 << 24) && (int64_t)g->nnz * 4 < (int64_t)1 << 32;
+  for (int64_t ld : {ldx, ldy, add ? ld_add : 0, mask ? ld_mask : 0, sig_out ? ld_sig : 0, add2 ? ld_add2 : 0})
+    narrow = narrow && ld * 4 < (1 << 24) && (int64_t)g->n_nodes * ld * 4 < (int64_t)1 << 32;
+  if (narrow) return launch_vec<true>(a, transpose, vec, nc, blocks, stream, g->nnz);
+  return launch_vec<false>(a, transpose, vec, nc, blocks, stream, g->nnz);
 }
 
 }  // namespace cpra

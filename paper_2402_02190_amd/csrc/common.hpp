@@ -60,6 +60,14 @@ class ProfScope {
   size_t idx_ = 0;
 };
 
+// 1 / x for x in [1, 2] (or NaN), rounded like the division: the reciprocal's estimate
+// corrected by its own residual, without the scaling and fix-up that the general
+// division needs (equal for every such x).
+__device__ __forceinline__ float recip_1_2(float x) {
+  const float r = __builtin_amdgcn_rcpf(x);
+  return fmaf(fmaf(-x, r, 1.0f), r, r);
+}
+
 inline hipStream_t as_stream(cpra_stream_t s) { return reinterpret_cast<hipStream_t>(s); }
 
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
