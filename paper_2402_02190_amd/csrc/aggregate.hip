@@ -66,10 +66,13 @@ __device__ inline void scale(typename Vec<VEC>::T& v, float s) {
 
 constexpr double kStreamOutBytes = 32.0 * 1024 * 1024;
 
+constexpr int kSlice = 32;  // columns of a slice: one 128-byte line of a row
+
 struct AggArgs {
   int n;
   int width;
   int lpr_log2;
+  int slices_log2;  // column slices dealt to the XCDs (0: whole rows)
   int relu;
   const int32_t* row_ptr;
   const int32_t* col_idx;
@@ -133,7 +136,7 @@ __device__ inline float sigmoid_of(float z) {
 // in bytes below 2^24): one 24-bit multiply-add per gather, entries and factors loaded
 // together.  252 graphs of 2,750 nodes, mean degree 7, 32 columns: 129 -> 113 us, and
 // transposed 79 -> 73 us.  On one large 20-regular graph the L2 misses bound it
-// (100,000 x 128: 137 -> 133 us, 7.7 TB/s of rows).
+// (100,000 x 128: 137 us, 7.5 TB/s of rows; in column slices 103).
 template <int VEC, int NC, bool TRANS, bool NARROW, int CH>
 __device__ __forceinline__ void agg_unit(const AggArgs& a, int unit) {
   using V = typename Vec<VEC>::T;
@@ -270,10 +273,26 @@ __device__ __forceinline__ void agg_unit(const AggArgs& a, int unit) {
   }
 }
 
-// One block per row block, in XCD order.
+// One block per row block, in XCD order; with column slices, XCD x takes slice
+// x % slices of its share of the rows, so that the table it gathers from is that much
+// smaller against its L2.
 template <int VEC, int NC, bool TRANS, bool NARROW, int CH>
 __global__ __launch_bounds__(256) void k_aggregate(AggArgs a) {
-  agg_unit<VEC, NC, TRANS, NARROW, CH>(a, xcd_unit(blockIdx.x, gridDim.x));
+  int unit = xcd_unit(blockIdx.x, gridDim.x);
+  if (a.slices_log2) {
+    const int xcd = blockIdx.x & 7;
+    const int c0 = (xcd & ((1 << a.slices_log2) - 1)) * kSlice;
+    unit = (xcd >> a.slices_log2) * (int)(gridDim.x >> 3) + (int)(blockIdx.x >> 3);
+    a.X += c0;
+    a.Y += c0;
+    if (a.add) a.add += c0;
+    if (a.add2) a.add2 += c0;
+    if (a.bias) a.bias += c0;
+    if (a.mask) a.mask += c0;
+    if (a.sig_out) a.sig_out += c0;
+    a.width = kSlice;
+  }
+  agg_unit<VEC, NC, TRANS, NARROW, CH>(a, unit);
 }
 
 // Persistent: at most the resident blocks, each taking row blocks from the queue.
@@ -322,14 +341,18 @@ cpra_status launch_nc(const AggArgs& a, int nc, int blocks, hipStream_t stream, 
     }
   };
   // Chunks of 8 entries (of 4 for four vectors and more per lane, for the registers).
-  // With two vectors per lane and a table of twice an XCD's L2 and more, 8 gathers per
-  // lane in flight only push each other's lines out: 20-regular, 100,000 x 32: 44 us
+  // Column slices take chunks of 2 (100,000 x 128: 103 us, with 4 111, with 8 121, with
+  // 1 112).  With two vectors per lane and a table of twice an XCD's L2 and more, 8
+  // gathers per lane in flight only push each other's lines out: 20-regular, 100,000 x 32: 44 us
   // with chunks of 8 and 33 with chunks of 2 (transposed 45 and 42), 10,000 x 256: 20.6
   // and 17.4.  Below, the latency counts: 10,000 x 128: 10.2 and 11.7, 2,000 x 64: 4.9
   // and 5.6.
-  const bool misses = (double)a.n * a.ldx * 4.0 > 8.0 * 1024 * 1024;
+  const bool misses = (double)a.n * a.width * 4.0 > 8.0 * 1024 * 1024;
   switch (nc) {
-    case 1: launch(std::integral_constant<int, 1>{}, std::integral_constant<int, 8>{}); break;
+    case 1:
+      if (a.slices_log2) launch(std::integral_constant<int, 1>{}, std::integral_constant<int, 2>{});
+      else launch(std::integral_constant<int, 1>{}, std::integral_constant<int, 8>{});
+      break;
     case 2:
       if (misses) launch(std::integral_constant<int, 2>{}, std::integral_constant<int, 2>{});
       else launch(std::integral_constant<int, 2>{}, std::integral_constant<int, 8>{});
@@ -342,6 +365,30 @@ cpra_status launch_nc(const AggArgs& a, int nc, int blocks, hipStream_t stream, 
   }
   CPRA_CHECK_LAUNCH("aggregate");
   return CPRA_OK;
+}
+
+// Slices of 32 columns, one 128-byte line of a row, dealt to the XCDs: the XCDs of a
+// slice share the rows, and each gathers from n lines instead of n rows, of which its
+// 4 MB L2 holds that much more; a row's entries are read once per slice.  (One graph:
+// the rows of a batch's graphs are dealt to the XCDs, and their tables are small.)
+// Measured whole rows against slices, us, transposed gather in brackets:
+//   256 columns from 8 MB on:  10,000 nodes, 5-regular 9.1, 6.7 (9.2, 6.8);
+//                              50,000, 20-regular 130, 93 (135, 105)
+//   128 columns from 12 MB on: 30,000, 5-regular 13.4, 11.1 (13.8, 11.5); 100,000,
+//                              20-regular 133, 102 (141, 116); at 10 MB 16.7, 18.6
+//   64 columns from 16 MB on and mean degree 12: 100,000, 20-regular 59, 52 (69, 57);
+//                              50,000, 20-regular 22.0, 24.0; 100,000, 5-regular 22.0, 22.9
+// Sparse graphs past 131,072 nodes keep whole rows (200,000, 5-regular, 128 columns: 83,
+// 84 (85, 87)).
+int slices_log2_of(const cpra_csr* g, int width, const float* X, int64_t ldx) {
+  const bool dense = g->nnz >= 12 * (int64_t)g->n_nodes;
+  const double mb = (double)g->n_nodes * width * 4.0 / (1024 * 1024);
+  if (g->n_graphs != 1 || ldx % kSlice != 0 || !aligned(X, 4 * kSlice)) return 0;
+  if (!dense && g->n_nodes > 131072) return 0;
+  if (width == 8 * kSlice) return mb >= 8 ? 3 : 0;
+  if (width == 4 * kSlice) return mb >= 12 ? 2 : 0;
+  if (width == 2 * kSlice) return dense && mb >= 16 ? 1 : 0;
+  return 0;
 }
 
 template <bool NARROW>
@@ -383,8 +430,11 @@ cpra_status aggregate(const cpra_csr* g, bool transpose, int width, const float*
   // 20-regular 100,000-node aggregation 167 -> 151 us.  On sparser graphs
   // (mean degree ~7) the one-vector layout was faster (150 vs 178 us).
   const int per_lane = g->nnz >= 12 * (int64_t)g->n_nodes ? 2 : 1;
+  const bool queued = queue && persistent_enabled();
+  const int slices_log2 = vec == 4 && !queued ? slices_log2_of(g, width, X, ldx) : 0;
+  if (slices_log2) units = kSlice / vec;
   int lpr = 1;
-  while (per_lane * lpr < units && lpr < 64) lpr <<= 1;
+  while ((slices_log2 ? 1 : per_lane) * lpr < units && lpr < 64) lpr <<= 1;
   int lpr_log2 = 0;
   while ((1 << lpr_log2) < lpr) ++lpr_log2;
   int need = (int)ceil_div(units, lpr);
@@ -393,10 +443,11 @@ cpra_status aggregate(const cpra_csr* g, bool transpose, int width, const float*
   if (nc > 16) CPRA_FAIL(CPRA_ERR_SHAPE, "aggregate: width %d exceeds 4096", width);
   int rows_per_block = 4 * (64 / lpr);
   const int units_rb = (int)ceil_div(g->n_nodes, rows_per_block);
-  int blocks = (int)xcd_grid(units_rb);
-  AggArgs a{g->n_nodes, width, lpr_log2, relu ? 1 : 0, g->row_ptr, g->col_idx, g->inv_deg,
+  const int blocks =
+      slices_log2 ? 8 * (int)ceil_div(units_rb, 8 >> slices_log2) : (int)xcd_grid(units_rb);
+  AggArgs a{g->n_nodes, width, lpr_log2, slices_log2, relu ? 1 : 0, g->row_ptr, g->col_idx, g->inv_deg,
             g->col_inv_deg, X, ldx, Y, ldy, add, ld_add, bias, mask, ld_mask, sig_out, ld_sig, add2, ld_add2,
-            (unsigned)(g->nnz * 4), (queue && persistent_enabled()) ? queue : nullptr, units_rb, 1,
+            (unsigned)(g->nnz * 4), queued ? queue : nullptr, units_rb, 1,
             (double)g->n_nodes * width * 4.0 > kStreamOutBytes ? 1 : 0};
   // 32-bit byte offsets where every one fits, from 24-bit factors.
   bool narrow = g->n_nodes < (1 << 24) && (int64_t)g->nnz * 4 < (int64_t)1 << 32;

@@ -26,7 +26,7 @@ def graph(name):
 def fma32(a, b, c):
     """float32 fma: the product of two float32 is exact in float64, whose rounded sum
     rounds again only on a tie of the 24th bit, which these inputs do not reach."""
-    return (a.astype(np.float64) * b.astype(np.float64) + c.astype(np.float64)).astype(np.float32)
+    return (np.asarray(a, np.float64) * np.asarray(b, np.float64) + np.asarray(c, np.float64)).astype(np.float32)
 
 
 @pytest.mark.parametrize("ld", ["tight", "padded", "wide"])
@@ -64,3 +64,31 @@ def test_chunked_sums_are_exact(name, width, ld):
         assert np.array_equal(Y.cpu().numpy(), want), f"transpose={transpose}"
         api.aggregate_mean(dg, X, Y, transpose=transpose, add=to_dev(add), relu=True)
         assert np.array_equal(Y.cpu().numpy(), np.maximum(want + add, 0)), f"addend, transpose={transpose}"
+
+
+@pytest.mark.parametrize("n,degree,width", [(8200, 3, 256), (24_600, 5, 128), (65_600, 13, 64)])
+def test_column_slices_are_exact(n, degree, width):
+    """Tables past the sizes from which the columns are dealt to the XCDs in slices: rows
+    that no block of a slice may miss or do twice, every epilogue operand.  The sums are
+    taken here over all rows at once, one entry of every row after the other."""
+    need_gpu()
+    from paper_2402_02190_amd import api
+    g = random_regular_graph(n, degree, 1)
+    say(f"column slices n={n} degree={degree} width={width}")
+    dg = api.DeviceGraph.from_csr(g)
+    rng = np.random.default_rng(n)
+    Xh = (rng.integers(-2048, 2048, (n, width)) / 64).astype(np.float32)
+    add, mask = (rng.standard_normal((n, width)).astype(np.float32) for _ in range(2))
+    bias = rng.standard_normal(width).astype(np.float32)
+    X, Y = to_dev(Xh), torch.full((n, width + 32), 7.0, device="cuda")
+    inv = np.float32(1.0) / np.float32(degree)
+    cols = g.col_idx.reshape(n, degree)
+    total, scaled = np.zeros((n, width), np.float32), np.zeros((n, width), np.float32)
+    for e in range(degree):
+        total = total + Xh[cols[:, e]]
+        scaled = fma32(np.float32(inv), Xh[cols[:, e]], scaled)
+    api.aggregate_mean(dg, X, Y[:, :width], add=to_dev(add), bias=to_dev(bias), relu=True)
+    assert np.array_equal(Y[:, :width].cpu().numpy(), np.maximum(total * inv + add + bias, 0))
+    api.aggregate_mean(dg, X, Y[:, :width], transpose=True, add=to_dev(add), mask=to_dev(mask))
+    assert np.array_equal(Y[:, :width].cpu().numpy(), np.where(mask > 0, scaled + add, 0))
+    assert torch.all(Y[:, width:] == 7.0)
