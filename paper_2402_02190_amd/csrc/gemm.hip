@@ -122,7 +122,8 @@ const char* kCfgNames[kNumCfgs] = {"64x64x32_w2x2",   "64x64x32_w2x1", "64x64x32
                                    "128x32x32_w4x1_bf3", "32x64x32_w1x2_bf3",
                                    "32x32x32_w1x1_bf3", "64x64x16_w2x1_bf3", "128x128x32_rows_bf3", "128x64x32_rows_bf3", "128x32x32_rows_bf3",
                                    "64x64x32_rows_bf3", "32x32x32_rows_bf3", "64x64x32_w2x2_ord", "128x64x32_w2x2_ord", "32x64x32_w1x2_ord",
-                                   "32x32x32_w1x1_ord", "128x128x32_w2x4_ord", "128x32x32_w4x1_ord"};
+                                   "32x32x32_w1x1_ord", "128x128x32_w2x4_ord", "128x32x32_w4x1_ord",
+                                   "16x16x32_direct_ord"};
 
 struct Plan {
   int cfg, splits;
@@ -184,6 +185,11 @@ int heuristic_splits(const GemmProblem* probs, int n, const Cfg& c) {
 //    (two per CU; 100,000x128, K = 256: 49, ordered 63, before 97, best old 78;
 //    704,000x64, K = 64: 76, 86, 190, 111), 64x64 below (10,000x256, K = 512: 25.5,
 //    ordered 31, 128x64 rows 27, before 46, best old 35).
+//  * The smallest of those (alone, back to back in a graph): one 16x16 tile per
+//    wavefront.  Up to 512 tiles: 100x64, K = 64: 4.4, ordered 4.5; 500x64, K = 128: 5.5
+//    and 5.9; 2,000x64, K = 128: 5.7 and 5.95; 4,000x64, K = 64: 5.0 and 4.7.  Weight
+//    gradients up to 2,048 tiles and splits: 32x64 over K = 100: 4.6 and 5.6; 64x64 over
+//    1,000 with 8 splits: 6.8 and 8.2.
 //  * Weight gradients: the split count brings 64x64 tiles to 512 blocks with 4 K steps
 //    at least (128x128 over K = 100,000 in 128: 39 split, 44 ordered, 41 best old);
 //    up to 32 rows of output, 32-row tiles.
@@ -200,6 +206,11 @@ Plan heuristic_plan(bool a_t, const GemmProblem* probs, int n, bool can_split) {
   Plan p{kOrd64, 1};
   if (can_split) p.splits = heuristic_splits(probs, n, kCfgs[kOrd64]);
   if (ordered || tiles64 * p.splits < 256) {
+    const int64_t tiles16 = tiles_of(probs, n, kCfgs[kDirect]);
+    if (!probs[0].group_mode && !bias_grad && tiles16 * p.splits <= (a_t ? 2048 : 64)) {
+      p.cfg = kDirect;
+      return p;
+    }
     // a bias gradient keeps the four slices per row of the 256- and 128-thread tiles
     if (a_t) p.cfg = m_rows > 32 ? kOrd64 : n_cols > 32 || bias_grad ? kOrd32x64 : kOrd32;
     else if (n_cols <= 32) p.cfg = tiles_of(probs, n, kCfgs[kOrd128x32]) >= 512 ? kOrd128x32 : kOrd32;

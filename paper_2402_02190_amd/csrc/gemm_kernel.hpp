@@ -1027,13 +1027,14 @@ constexpr Cfg kCfgs[] = {
     {32, 32, 32, 1, 1},    // 48
     {128, 128, 32, 2, 4},  // 49
     {128, 32, 32, 4, 1},   // 50
+    {16, 16, 32, 1, 1},    // 51: 64 threads, operands straight from memory
 };
 constexpr int kNumCfgs = sizeof(kCfgs) / sizeof(kCfgs[0]);
 constexpr int kFirstSplit = 32;  // configurations from here on are those of gemm_split.hpp
 constexpr int kFirstRows = 40;   // ... and from here on take A [M, K] (k_gemm_rows)
 constexpr int kSplit64 = 32, kSplit32x64 = 37, kSplit32 = 38, kRows128x64 = 41, kRows128x32 = 42, kRows32 = 44;
 constexpr int kFirstOrdered = 45;  // FP32 MFMAs, sums over k in order
-constexpr int kOrd64 = 45, kOrd128x64 = 46, kOrd32x64 = 47, kOrd32 = 48, kOrd128x32 = 50;
+constexpr int kOrd64 = 45, kOrd128x64 = 46, kOrd32x64 = 47, kOrd32 = 48, kOrd128x32 = 50, kDirect = 51;
 
 // index of a row-tile height in LaunchArgs::row_maps
 constexpr int bm_index(int bm) { return bm == 32 ? 0 : bm == 64 ? 1 : 2; }

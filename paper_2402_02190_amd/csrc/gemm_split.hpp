@@ -791,6 +791,156 @@ __global__ __launch_bounds__(64 * WM, BN >= 64 ? 2 : 4) void k_gemm_rows(LaunchA
 #endif
 }
 
+// 16 k of one operand of k_gemm_direct: x[s] of lane l is the value of row (column)
+// l % 16 at k = g + 4 s + l / 16; k from `left` on and rows with `edge` read as 0.
+// K-contiguous operands are read as one float4 per lane, k = g + 4 (l / 16) .., whose 4x4
+// blocks over the quarters of the wavefront are then transposed.
+template <bool KC, bool VEC>
+__device__ __forceinline__ void direct_operand(__amdgpu_buffer_rsrc_t rs, unsigned edge, unsigned ld4, int l16,
+                                               int quad, int g, int left, float* x) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  if constexpr (KC && VEC) {
+    const int k = g + 4 * quad;
+    const u32x4 v = buf4(rs, (l16 * ld4 + 4u * k) | edge | (k < left ? 0u : 0x80000000u));
+    const auto p02 = __builtin_amdgcn_permlane32_swap(v[0], v[2], false, false);
+    const auto p13 = __builtin_amdgcn_permlane32_swap(v[1], v[3], false, false);
+    const auto p01 = __builtin_amdgcn_permlane16_swap(p02[0], p13[0], false, false);
+    const auto p23 = __builtin_amdgcn_permlane16_swap(p02[1], p13[1], false, false);
+    x[0] = __uint_as_float(p01[0]);
+    x[1] = __uint_as_float(p01[1]);
+    x[2] = __uint_as_float(p23[0]);
+    x[3] = __uint_as_float(p23[1]);
+  } else {
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const int k = g + 4 * s + quad;
+      x[s] = buf1(rs, (KC ? l16 * ld4 + 4u * k : k * ld4 + 4u * l16) | edge | (k < left ? 0u : 0x80000000u));
+    }
+  }
+#endif
+}
+
+// Small products: a wavefront computes one 16x16 tile straight from global memory, every
+// operand of 64 k in flight at once, with the 16x16x4 FP32 MFMA (whose sums run over k in
+// order, like those of the 32x32x2: the bits are the same).  A launch of a few dozen
+// 32x32 tiles lasts as long as one wavefront takes to find its work and to issue a tile's
+// loads, LDS traffic and MFMAs; here that is a quarter, with no barrier, on four times
+// as many CUs.  Back to back in a graph: C = A^T B, 32x64 over K = 100: 5.6 -> 4.6 us;
+// A B^T, 100x64, K = 64: 4.5 -> 4.4 (2.7 of them are an empty kernel's).
+template <bool A_T, bool B_T, bool VEC>
+__global__ __launch_bounds__(64) void k_gemm_direct(LaunchArgs args) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  constexpr int BK = 32, CHUNK = 64, GROUP = 16;  // K step of the split ranges, k in flight, k per branch
+  // Blocks: column tile within problem, row tile, split (no divisions, which cost as much
+  // as the tile's loads).
+  Work w{};
+  int tn = blockIdx.x;
+  while (tn >= args.grid_x) {
+    tn -= args.grid_x;
+    ++w.prob;
+  }
+  w.split = blockIdx.z;
+  const ProbDev& P = args.p[w.prob];
+  if ((int)blockIdx.y >= P.tiles_m || tn >= P.tiles_n) return;
+  w.m0 = blockIdx.y * 16;
+  w.n0 = tn * 16;
+  w.m_lim = P.M;
+  w.kn0 = P.K[0];
+  w.kn1 = P.n_pieces > 1 ? P.K[1] : 0;
+  w.C = P.C;
+  w.bias = P.bias;
+  const int lane = threadIdx.x;
+  const int l16 = lane & 15, quad = lane >> 4;
+  const int m_valid = min(16, w.m_lim - w.m0), n_valid = min(16, P.N - w.n0);
+
+  const int nt0 = (w.kn0 + BK - 1) / BK;
+  const int KT = nt0 + (w.kn1 + BK - 1) / BK;
+  const int per_split = args.splits == 1 ? KT : __builtin_amdgcn_readfirstlane((KT + args.splits - 1) / args.splits);
+  const int kt_begin = min(KT, w.split * per_split);
+  const int kt_end = min(KT, kt_begin + per_split);
+
+  // The lane's results are rows 4 quad .. + 3 of column l16; their addends are loaded first.
+  const int row = w.m0 + 4 * quad, col = w.n0 + l16;
+  const bool final_ = args.splits == 1;
+  bool ok[4];
+  float add[4], old[4], msk[4], bias = 0.f;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    ok[i] = l16 < n_valid && 4 * quad + i < m_valid;
+    add[i] = old[i] = msk[i] = 0.f;
+    if (!final_ || !ok[i]) continue;
+    if (P.add) add[i] = P.add[(int64_t)(row + i) * P.ld_add + col];
+    if (P.beta != 0.f) old[i] = w.C[(int64_t)(row + i) * P.ldc + col];
+    if (P.mask) msk[i] = P.mask[(int64_t)(row + i) * P.ld_mask + col];
+  }
+  if (final_ && w.bias && l16 < n_valid) bias = w.bias[col];
+
+  typedef float floatx4 __attribute__((ext_vector_type(4)));
+  floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+  // k in [b, e) of one piece.  Rows and columns past the edge, and k past the end, are
+  // past the buffers' ranges (bit 31) and read as 0.
+  auto piece = [&](const float* A, const float* B, int64_t lda, int64_t ldb, int b, int e) {
+    const unsigned la = 4u * (unsigned)lda, lb = 4u * (unsigned)ldb;
+    const unsigned a0 = l16 < m_valid ? 0u : 0x80000000u, b0 = l16 < n_valid ? 0u : 0x80000000u;
+    auto load = [&](int k0, float (&x)[CHUNK / 4], float (&y)[CHUNK / 4]) {
+      const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(
+          (void*)(A + (A_T ? (int64_t)k0 * lda + w.m0 : (int64_t)w.m0 * lda + k0)), (short)0, 0x7fffffff, 0x00020000);
+      const __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc(
+          (void*)(B + (B_T ? (int64_t)w.n0 * ldb + k0 : (int64_t)k0 * ldb + w.n0)), (short)0, 0x7fffffff, 0x00020000);
+#pragma unroll
+      for (int g = 0; g < CHUNK; g += GROUP) {
+        if (k0 + g >= e) break;
+        direct_operand<!A_T, VEC>(ra, a0, la, l16, quad, g, e - k0, x + g / 4);
+        direct_operand<B_T, VEC>(rb, b0, lb, l16, quad, g, e - k0, y + g / 4);
+      }
+    };
+    auto multiply = [&](int k0, const float (&x)[CHUNK / 4], const float (&y)[CHUNK / 4]) {
+#pragma unroll
+      for (int g = 0; g < CHUNK; g += GROUP) {
+        if (k0 + g >= e) break;
+#pragma unroll
+        for (int s = g / 4; s < (g + GROUP) / 4; ++s)
+          acc = __builtin_amdgcn_mfma_f32_16x16x4f32(x[s], y[s], acc, 0, 0, 0);
+      }
+    };
+    float x[2][CHUNK / 4] = {}, y[2][CHUNK / 4] = {};
+    if (b < e) load(b, x[0], y[0]);
+    for (int k0 = b; k0 < e; k0 += 2 * CHUNK) {
+      if (k0 + CHUNK < e) load(k0 + CHUNK, x[1], y[1]);
+      multiply(k0, x[0], y[0]);
+      if (k0 + CHUNK >= e) break;
+      if (k0 + 2 * CHUNK < e) load(k0 + 2 * CHUNK, x[0], y[0]);
+      multiply(k0 + CHUNK, x[1], y[1]);
+    }
+  };
+  piece(P.A[0], P.B[0], P.lda[0], P.ldb[0], min(w.kn0, kt_begin * BK), min(w.kn0, kt_end * BK));
+  if (P.n_pieces > 1)
+    piece(P.A[1], P.B[1], P.lda[1], P.ldb[1], max(0, min(w.kn1, (kt_begin - nt0) * BK)),
+          max(0, min(w.kn1, (kt_end - nt0) * BK)));
+
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    if (!ok[i]) continue;
+    float v = acc[i];
+    if (!final_) {
+      partial_of<0>(args, w)[(int64_t)(row + i) * P.n_eff + col] = v;
+      continue;
+    }
+    if (w.bias) v += bias;
+    if (P.add) v += add[i];
+    if (P.beta != 0.f) v += P.beta * old[i];
+    if (P.relu) v = fmaxf(v, 0.f);
+    if (P.mask) v = msk[i] > 0.f ? v : 0.f;
+    w.C[(int64_t)(row + i) * P.ldc + col] = v;
+    if (P.sig_out) {
+      const float z = expf(-fabsf(v));
+      const float s = recip_1_2(1.0f + z);
+      P.sig_out[(int64_t)(row + i) * P.ld_sig + col] = v >= 0.0f ? s : z * s;
+    }
+  }
+#endif
+}
+
 // Whether every K-contiguous operand may be read as float4s.
 inline bool split_vec(const LaunchArgs& args, bool a_t, bool b_t) {
   for (int i = 0; i < args.n_prob; ++i) {
@@ -846,6 +996,33 @@ void launch_rows(LaunchArgs& args, hipStream_t stream) {
   }
 }
 
+// Grouped products, those with a bias gradient and the tallest ones take the 32-row tiles instead.
+template <bool A_T, bool B_T, int GM>
+void launch_direct(LaunchArgs& args, hipStream_t stream) {
+  if constexpr (GM == 0) {
+    int64_t rows = 0;
+    for (int i = 0; i < args.n_prob; ++i) rows = std::max<int64_t>(rows, args.p[i].M);
+    if (!wants_bias_grad(args) && rows <= 16 * 65535) {  // the grid's limit
+      int tm = 0, tn = 0;
+      for (int i = 0; i < args.n_prob; ++i) {
+        ProbDev& d = args.p[i];
+        d.tiles_m = (int)ceil_div(d.M, 16);
+        d.tiles_n = (int)ceil_div(d.N, 16);
+        tm = max(tm, d.tiles_m);
+        tn = max(tn, d.tiles_n);
+      }
+      args.grid_x = tn;
+      const dim3 grid((unsigned)(tn * args.n_prob), (unsigned)tm, (unsigned)args.splits);
+      if (split_vec(args, A_T, B_T))
+        hipLaunchKernelGGL((k_gemm_direct<A_T, B_T, true>), grid, dim3(64), 0, stream, args);
+      else
+        hipLaunchKernelGGL((k_gemm_direct<A_T, B_T, false>), grid, dim3(64), 0, stream, args);
+      return;
+    }
+  }
+  launch_oct<32, 64, 32, 1, 2, false, A_T, B_T, GM>(args, stream);
+}
+
 template <bool A_T, bool B_T, int GM>
 void launch_split_any(int cfg, LaunchArgs& args, hipStream_t stream) {
   switch (cfg) {
@@ -871,6 +1048,7 @@ void launch_split_any(int cfg, LaunchArgs& args, hipStream_t stream) {
     case 42: launch_rows<32, 4, A_T, B_T, GM>(args, stream); break;
     case 43: launch_rows<64, 2, A_T, B_T, GM>(args, stream); break;
     case 44: launch_rows<32, 1, A_T, B_T, GM>(args, stream); break;
+    case kDirect: launch_direct<A_T, B_T, GM>(args, stream); break;
     default: break;
   }
 }
