@@ -294,8 +294,8 @@ struct SideStream {
   hipStream_t stream;
   hipEvent_t ev[2];
 };
-bool overlap_enabled();  // unless CPRA_OVERLAP=0 in the environment
-cpra_status get_side_stream(SideStream** out);
+// Null outside captures and with CPRA_OVERLAP=0 in the environment.
+cpra_status side_stream_for(hipStream_t main, SideStream** out);
 cpra_status fork_to(SideStream* s, hipStream_t main);
 cpra_status fork_mark(SideStream* s, hipStream_t main);
 cpra_status fork_wait(SideStream* s);

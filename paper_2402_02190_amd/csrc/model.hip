@@ -593,7 +593,7 @@ cpra_status cpra_model_backward(const cpra_csr* g, const cpra_model_cfg* cfg, co
   if (ws == nullptr || ws_bytes < p.total)
     CPRA_FAIL(CPRA_ERR_WORKSPACE, "model_backward: workspace %zu < %zu bytes", ws_bytes, p.total);
   SideStream* side = nullptr;
-  if (overlap_enabled()) CPRA_CHECK(get_side_stream(&side));
+  CPRA_CHECK(side_stream_for(as_stream(stream), &side));
   CPRA_CHECK(backward_impl(g, p, params, dZ, lddz, grads, ws, as_stream(stream), side, false, false));
   if (side) CPRA_CHECK(join_from(side, as_stream(stream)));
   return CPRA_OK;
@@ -654,7 +654,7 @@ cpra_status cpra_train_step(const cpra_csr* g, const cpra_step_cfg* cfg, float* 
   hipStream_t st = as_stream(stream);
   const int S = cfg->model.S;
   SideStream* side = nullptr;
-  if (overlap_enabled()) CPRA_CHECK(get_side_stream(&side));
+  CPRA_CHECK(side_stream_for(st, &side));
   void* loss_ws = static_cast<char*>(ws) + model_bytes;
   CPRA_CHECK(forward_impl(g, p, params, Z, S, ws, st, true));
   CPRA_CHECK(loss_fwd_bwd(g, &lc, Z, S, fptr(ws, p.p_off), S, dZ, S, nullptr, loss_ws,
