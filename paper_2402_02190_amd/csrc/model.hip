@@ -520,6 +520,19 @@ cpra_status backward_impl(const cpra_csr* g, const Plan& p, const float* params,
   return CPRA_OK;
 }
 
+// Whether a backward forks its weight gradients to the side stream (in captures only:
+// side_stream_for).  From two trained layers and a million values per layer input on: a
+// forked graph of less costs more in dependencies between its queues than it overlaps.
+// Steps, forked and on one stream: 10,000 nodes, 2x256: 0.214 and 0.225 ms; 86,000
+// nodes, 2x64: 0.236 and 0.250; 100,000 nodes, 3x128: 1.24 and 1.26.  One layer of
+// 100,000x128: 408 and 409 us, of 693,000x64: 837 and 830; two layers of 2,000x64,
+// launched alone: 200 and 115 us; ten steps of 100x32: 705 and 694.
+bool worth_forking(const Plan& p, int n_nodes) {
+  int64_t width = 0;
+  for (int k = p.train_from; k < p.L; ++k) width = std::max<int64_t>(width, p.layer[k].in);
+  return p.L - p.train_from >= 2 && n_nodes * width >= (int64_t)1 << 20;
+}
+
 cpra_status check_graph_and_model(const cpra_csr* g, const cpra_model_cfg* cfg, const char* who) {
   CPRA_CHECK(check_csr(g, who, true, false));
   CPRA_CHECK(check_model_cfg(cfg));
@@ -593,7 +606,7 @@ cpra_status cpra_model_backward(const cpra_csr* g, const cpra_model_cfg* cfg, co
   if (ws == nullptr || ws_bytes < p.total)
     CPRA_FAIL(CPRA_ERR_WORKSPACE, "model_backward: workspace %zu < %zu bytes", ws_bytes, p.total);
   SideStream* side = nullptr;
-  CPRA_CHECK(side_stream_for(as_stream(stream), &side));
+  if (worth_forking(p, g->n_nodes)) CPRA_CHECK(side_stream_for(as_stream(stream), &side));
   CPRA_CHECK(backward_impl(g, p, params, dZ, lddz, grads, ws, as_stream(stream), side, false, false));
   if (side) CPRA_CHECK(join_from(side, as_stream(stream)));
   return CPRA_OK;
@@ -654,7 +667,7 @@ cpra_status cpra_train_step(const cpra_csr* g, const cpra_step_cfg* cfg, float* 
   hipStream_t st = as_stream(stream);
   const int S = cfg->model.S;
   SideStream* side = nullptr;
-  CPRA_CHECK(side_stream_for(st, &side));
+  if (worth_forking(p, g->n_nodes)) CPRA_CHECK(side_stream_for(st, &side));
   void* loss_ws = static_cast<char*>(ws) + model_bytes;
   CPRA_CHECK(forward_impl(g, p, params, Z, S, ws, st, true));
   CPRA_CHECK(loss_fwd_bwd(g, &lc, Z, S, fptr(ws, p.p_off), S, dZ, S, nullptr, loss_ws,
