@@ -5,7 +5,7 @@
         --output-format csv -d D -o run -- python bench.py --pmc-pass ...
     python -m paper_2402_02190_amd.mfma_counters --dir D --workload C2 --out FILE --command "..."
 
-Per kernel instantiation (dispatches of ``k_gemm<...>``): the MFMA instructions
+Per kernel instantiation (dispatches of ``k_gemm<...>``, ``k_gemm_oct<...>``, ``k_gemm_rows<...>``): the MFMA instructions
 and MFMA-busy cycles per dispatch (summed over all SIMDs by the hardware; a
 v_mfma_f32_32x32x2f32 keeps its SIMD's matrix core busy 64 cycles), and the
 utilisation busy / (SIMDs x clock x dispatch duration) with the dispatch's
@@ -40,8 +40,8 @@ def _rows(d: str):
 
 
 def short_name(name: str) -> str:
-    m = re.search(r"k_gemm<([^>]*)>", name)
-    return f"k_gemm<{m.group(1)}>" if m else name
+    m = re.search(r"k_gemm(?:_oct|_rows|_direct)?<[^>]*>", name)
+    return m.group(0) if m else name
 
 
 def dispatches(rows):
@@ -58,7 +58,7 @@ def summarise(rows):
     """Per k_gemm instantiation: averages over its dispatches."""
     groups = OrderedDict()
     for d in dispatches(rows).values():
-        if "k_gemm<" not in d["name"] or d.get("SQ_INSTS_MFMA", 0) <= 0:
+        if not re.search(r"k_gemm(_oct|_rows|_direct)?<", d["name"]) or d.get("SQ_INSTS_MFMA", 0) <= 0:
             continue
         groups.setdefault(short_name(d["name"]), []).append(d)
     out = []

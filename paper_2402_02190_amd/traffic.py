@@ -30,7 +30,8 @@ COPY_KERNEL = "__amd_rocclr_copyBuffer"
 CALIBRATION_BYTES = 1 << 30
 
 # family (as the library's profiler names it) -> source files of its kernel
-_SOURCES = {"gemm": ("gemm.hip", "gemm_kernel.hpp", "gemm_grouped.hip", "common.hpp"),
+_SOURCES = {"gemm": ("gemm.hip", "gemm_kernel.hpp", "gemm_plain.hip", "gemm_grouped.hip", "gemm_split.hpp",
+                     "gemm_split_nt.hip", "gemm_split_nn.hip", "gemm_split_tn.hip", "common.hpp"),
             "aggregate": ("aggregate.hip", "common.hpp"),
             "loss_fwd_bwd": ("loss.hip", "common.hpp"), "adam": ("adam.hip", "common.hpp")}
 
@@ -63,12 +64,28 @@ def kernel_pattern(family: str) -> re.Pattern:
         args = f"{bm}, {bn}, {bk}, {wm}, {wn}, {'true' if at == 't' else 'false'}, " \
                f"{'true' if bt == 't' else 'false'}, {pf}, {gm}"
         return re.compile(re.escape(f"k_gemm<{args}>"))
+    # the octet kernels: ..._bf3 and ..._ord -> k_gemm_oct<BM, BN, BK, WM, WN, A_T, B_T, VEC, SP, GM>,
+    # <BM>x<BN>x<BK>_rows_bf3 -> k_gemm_rows<BN, BM / 32, B_T, VEC, GM>, ..._direct_ord ->
+    # k_gemm_direct<A_T, B_T, VEC>
+    m = re.fullmatch(r"gemm_([nt])([nt])(_byrow|_byk)?_(\d+)x(\d+)x(\d+)_(w\d+x\d+_bf3|w\d+x\d+_ord|rows_bf3|direct_ord)",
+                     family)
+    if m:
+        at, bt, grp, bm, bn, bk, kind = m.groups()
+        gm = {None: 0, "_byrow": 1, "_byk": 2}[grp]
+        at, bt = (("false", "true")[x == "t"] for x in (at, bt))
+        if kind == "direct_ord":
+            return re.compile(rf"k_gemm_direct<{at}, {bt}, ")
+        if kind == "rows_bf3":
+            return re.compile(rf"k_gemm_rows<{bn}, {int(bm) // 32}, {bt}, (true|false), {gm}>")
+        wm, wn = re.match(r"w(\d+)x(\d+)", kind).groups()
+        sp = "true" if kind.endswith("_bf3") else "false"
+        return re.compile(rf"k_gemm_oct<{bm}, {bn}, {bk}, {wm}, {wn}, {at}, {bt}, (true|false), {sp}, {gm}>")
     if family == "gemm_splitk_reduce":
         return re.compile(r"k_gemm_splitk_reduce")
     if family == "aggregate":
-        return re.compile(r"k_aggregate<\d+, \d+, false>")
+        return re.compile(r"k_aggregate<\d+, \d+, false[,>]")
     if family == "aggregate_transposed":
-        return re.compile(r"k_aggregate<\d+, \d+, true>")
+        return re.compile(r"k_aggregate<\d+, \d+, true[,>]")
     if family == "loss_fwd_bwd":
         return re.compile(r"k_loss<")
     if family == "adam":
