@@ -71,7 +71,7 @@ def steps(trace_dir: str, bench_json: str, title: str, command: str, out: str) -
     trace = glob.glob(os.path.join(trace_dir, "**", "*kernel_trace.csv"), recursive=True)
     if fam and trace:
         rx = kernel_pattern(fam)
-        pat = rx.pattern.replace("\\d+", "*").replace("\\", "")
+        pat = rx.pattern.replace("\\d+", "*").replace("(true|false)", "*").replace("[,>]", ">").replace("\\", "")
         with open(trace[0]) as f:
             d = [(int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) / 1e3
                  for r in csv.DictReader(f) if rx.search(r["Kernel_Name"])]
