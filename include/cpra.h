@@ -355,11 +355,12 @@ cpra_status cpra_adam_step(int64_t n, float* params, const float* grads, float* 
  * With step_counter non-NULL (a device int32 holding the number of steps
  * done, t - 1), gamma and Adam's t come from the device and the step
  * increments the counter, so the same enqueued work can be captured once and
- * replayed for every step.  The weight-gradient GEMMs and the loss-term
- * reduction run on a library-owned second stream of the current device,
- * forked from and joined back into `stream` by events (also when captured);
- * CPRA_OVERLAP=0 in the environment (read at every call) keeps all work on
- * `stream`.
+ * replayed for every step.  While `stream` is being captured, a network of
+ * two trained layers and more, with 2^20 input values per layer and more,
+ * runs its weight-gradient GEMMs and loss-term reduction on a library-owned
+ * second stream of the current device, forked from and joined back into
+ * `stream` by events; all other work stays on `stream`, and
+ * CPRA_OVERLAP=0 in the environment (read at every call) keeps that there too.
  * cpra_model_backward overlaps its weight gradients the same way.
  * ---------------------------------------------------------------------- */
 /* ------------------------------------------------------------------------
