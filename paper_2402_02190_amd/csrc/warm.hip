@@ -10,9 +10,9 @@
 // Storage: bfloat16 activations [N, width] row-major (raw uint16 bit
 // patterns, round-to-nearest-even from float32), float32 master weights and
 // gradients, float32 output logits.  Kernels:
-//  * k_node_features -- 16 lanes per node: triangle count by comparing every
-//    neighbour's list with the node's own (by binary search for large degrees; integer,
-//    exact), then the feature row [d/16, clustering, random channels, 0...];
+//  * k_node_features -- 16 lanes or a wavefront per node: triangle count by comparing
+//    every neighbour's list with the node's own (by binary search for large degrees;
+//    integer, exact), then the feature row [d/16, clustering, random channels, 0...];
 //  * k_mpnn_layer -- one forward layer: each wavefront gathers the neighbour means of
 //    its 32 rows (float32 sums in CSR order, one rounding) into the operands of
 //    v_mfma_f32_32x32x16_bf16, next to the rows themselves, while the weights (at most
@@ -79,25 +79,77 @@ __device__ __forceinline__ long long wedges_by_search(const int32_t* __restrict_
   return cnt;
 }
 
-// A wavefront takes 4 nodes, 16 lanes each.  Up to kCompareDegree neighbours a node's
-// own list sits in its lanes' registers, lane l walks the list of neighbour l (eight
-// entries in flight) and compares each entry with every own one, passed round by
-// shuffles: three dependent loads in all, where the search makes log2(d) more per
-// entry.  With a larger node among the four, they are done one after the other by
-// search (comparing costs d_i d_j, searching d_j log d_i).  N = 50,000, 5-regular:
-// 42 -> 10.7 us.
-constexpr int kCompareDegree = 32;
+// 2 T_i by LPN lanes for d <= LPN H neighbours: the node's own list sits in its lanes'
+// registers, lane l walks the list of neighbour l (eight entries in flight) and compares
+// each entry with every own one, passed round by shuffles: three dependent loads in all,
+// where the search makes log2(d) more per entry.  All 64 lanes call it; d = 0 gives 0.
+template <int LPN, int H>
+__device__ __forceinline__ int wedges_by_compare(const int32_t* __restrict__ row_ptr,
+                                                 const int32_t* __restrict__ col_idx, int b, int d, int l) {
+  int own[H], key[H], bj[H], ej[H];  // neighbours l, l + LPN, ..
+#pragma unroll
+  for (int h = 0; h < H; ++h) {
+    const int t = LPN * h + l;
+    own[h] = t < d ? col_idx[b + t] : -1;
+    key[h] = t > 0 && t < d && col_idx[b + t - 1] == own[h] ? -1 : own[h];  // a repeated entry matches once
+  }
+#pragma unroll
+  for (int h = 0; h < H; ++h) {
+    bj[h] = own[h] >= 0 ? row_ptr[own[h]] : 0;
+    ej[h] = own[h] >= 0 ? row_ptr[own[h] + 1] : 0;
+  }
+  int c = 0;
+#pragma unroll
+  for (int h = 0; h < H; ++h) {
+    for (int q = bj[h]; __any(q < ej[h]); q += 8) {
+      int x[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) x[u] = q + u < ej[h] ? col_idx[q + u] : -2;
+#pragma unroll
+      for (int p = 0; p < H; ++p)
+        for (int t = 0; t < LPN && __any(LPN * p + t < d); ++t) {
+          const int o = __shfl(key[p], t, LPN);
+#pragma unroll
+          for (int u = 0; u < 8; ++u) c += x[u] == o;
+        }
+    }
+  }
+  return c;  // this lane's share
+}
+
+// LPN lanes per node, by comparison up to 32 neighbours; the larger nodes of a wavefront
+// one after the other by all its lanes, by comparison up to kWideDegree, then by search
+// (comparing costs d_i d_j, searching d_j log d_i; 40-regular, N = 500: 27 us and 31,
+// 64-regular 64 and 52).  With 16 lanes per node a wavefront's four nodes lie a quarter
+// of the graph apart, so that a run of large ones is spread over as many wavefronts.
+//
+// Bound by the chain of dependent loads while the wavefronts fit the chip, then by the
+// comparisons.  16 lanes per node from 8,192 nodes on and up to a mean degree of 24, else
+// a wavefront per node (us, 16 lanes and 64; before both, by search alone, in brackets):
+//   5-regular    8,000 8.2, 7.9 (7.8); 32,000 8.1, 16.2 (22.8); 200,000 34, 89 (178)
+//   16-regular   8,000 10.6, 14.9 (19.9); 32,000 30, 42 (67)
+//   20-regular   2,000 19.9, 10.8 (16.0); 8,000 22.7, 23.1 (26.4); 32,000 55, 68 (91)
+//   40-regular   2,000 96, 27 (39); 32,000 232, 204 (332)
+//   100-regular  2,000 657, 214 (209); 16,000 1,359, 872 (849)
+//   random       9,000 of mean 28 120, 67 (80); 20,000 of mean 10 25.2, 29.0 (43.4), of
+//                mean 30 178, 129 (141)
+//   power law of mean 16 (largest degree 117 and 346): 2,000 147, 107 (112);
+//                20,000 504, 449 (469); 4.6 of mean with 3 hubs of 2,000: 2,466, 2,456 (2,471)
+constexpr int kWideDegree = 48;
+template <int LPN>
 __global__ __launch_bounds__(256) void k_node_features(int n, const int32_t* __restrict__ row_ptr,
                                                        const int32_t* __restrict__ col_idx,
                                                        int in_dim, int n_rand,
                                                        const float* __restrict__ rand,
                                                        int64_t ld_rand, uint16_t* __restrict__ feat,
                                                        int64_t ld_feat, int64_t* __restrict__ tri) {
+  constexpr int NPW = 64 / LPN;  // nodes per wavefront
   const int lane = threadIdx.x & 63;
-  const int sub = lane >> 4, l = lane & 15;
-  const int i0 = (blockIdx.x * 4 + (threadIdx.x >> 6)) * 4;
-  if (i0 >= n) return;  // uniform per wavefront
-  const int i = i0 + sub;
+  const int sub = lane / LPN, l = lane % LPN;
+  const int per = (n + NPW - 1) / NPW;
+  const int w = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (w >= per) return;  // uniform per wavefront
+  const int i = w + sub * per;
   int b = 0, e = 0;
   if (i < n) {
     b = row_ptr[i];
@@ -105,50 +157,26 @@ __global__ __launch_bounds__(256) void k_node_features(int n, const int32_t* __r
   }
   const int d = e - b;
   long long cnt = 0;  // sum over neighbours j of |N(i) n N(j)| = 2 T_i
-  if (!__any(d > kCompareDegree)) {
-    int own[2], key[2], bj[2], ej[2];  // neighbours l and l + 16
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int t = 16 * h + l;
-      own[h] = t < d ? col_idx[b + t] : -1;
-      key[h] = t > 0 && t < d && col_idx[b + t - 1] == own[h] ? -1 : own[h];  // a repeated entry matches once
-    }
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      bj[h] = own[h] >= 0 ? row_ptr[own[h]] : 0;
-      ej[h] = own[h] >= 0 ? row_ptr[own[h] + 1] : 0;
-    }
-    int c = 0;
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      for (int q = bj[h]; __any(q < ej[h]); q += 8) {
-        int x[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) x[u] = q + u < ej[h] ? col_idx[q + u] : -2;
-#pragma unroll
-        for (int p = 0; p < 2; ++p)
-          for (int t = 0; t < 16 && __any(16 * p + t < d); ++t) {
-            const int o = __shfl(key[p], t, 16);
-#pragma unroll
-            for (int u = 0; u < 8; ++u) c += x[u] == o;
-          }
-      }
-    }
-    cnt = c;
+  if constexpr (LPN == 16) {
+    if (__any(d > 0 && d <= 32)) cnt = wedges_by_compare<16, 2>(row_ptr, col_idx, b, d <= 32 ? d : 0, l);
 #pragma unroll
     for (int off = 8; off > 0; off >>= 1) cnt += __shfl_xor(cnt, off);
-  } else {
-    for (int t = 0; t < 4; ++t) {
-      long long c = wedges_by_search(row_ptr, col_idx, __shfl(b, 16 * t), __shfl(e, 16 * t), lane);
+  }
+  for (int t = 0; t < NPW; ++t) {
+    const int dt = __shfl(d, LPN * t);  // uniform, as the branches on it
+    if (LPN == 16 && dt <= 32) continue;
+    const int bt = __shfl(b, LPN * t);
+    long long c;
+    if (dt <= kWideDegree) c = wedges_by_compare<64, 1>(row_ptr, col_idx, bt, dt, lane);
+    else c = wedges_by_search(row_ptr, col_idx, bt, bt + dt, lane);
 #pragma unroll
-      for (int off = 32; off > 0; off >>= 1) c += __shfl_xor(c, off);
-      if (sub == t) cnt = c;
-    }
+    for (int off = 32; off > 0; off >>= 1) c += __shfl_xor(c, off);
+    if (sub == t) cnt = c;
   }
   if (i >= n) return;
   const long long T = cnt / 2;
   if (l == 0 && tri) tri[i] = T;
-  for (int c = l; c < in_dim; c += 16) {
+  for (int c = l; c < in_dim; c += LPN) {
     float v = 0.0f;
     if (c == 0) {
       v = (float)d * 0.0625f;
@@ -828,7 +856,9 @@ cpra_status cpra_node_features(const cpra_csr* g, int32_t in_dim, int32_t n_rand
                        (triangles ? 8.0 : 0.0) * g->n_nodes + 4.0 * (double)g->nnz +
                        4.0 * (g->n_nodes + 1.0);
   ProfScope ps("node_features", st, 0.0, bytes);
-  hipLaunchKernelGGL(k_node_features, dim3((unsigned)ceil_div(g->n_nodes, 16)), dim3(256), 0, st,
+  const bool four = g->n_nodes >= 8192 && g->nnz <= 24 * (int64_t)g->n_nodes;
+  auto* const kernel = four ? k_node_features<16> : k_node_features<64>;
+  hipLaunchKernelGGL(kernel, dim3((unsigned)ceil_div(g->n_nodes, four ? 16 : 4)), dim3(256), 0, st,
                      g->n_nodes, g->row_ptr, g->col_idx, in_dim, n_rand, rand, ld_rand, feat,
                      ld_feat, triangles);
   CPRA_CHECK_LAUNCH("node_features");

@@ -1,0 +1,50 @@
+"""Split GEMM configurations on operands near the ends of FP32's range, and on the
+shortest sums, against the FP32 MFMA loop of configuration 0.
+
+Bounds: the relative 2-norm error against FP64 may not pass that of the FP32 sums, or
+1e-7 where that is smaller (one rounding of the result is 3e-8).
+"""
+import numpy as np
+import pytest
+import torch
+
+from helpers import need_gpu, to_dev
+pytestmark = pytest.mark.gpu
+
+CONFIGS = [*range(32, 45)]
+
+
+def api():
+    need_gpu()
+    from paper_2402_02190_amd import api as a
+    return a
+
+
+def run(a, cfg, A, B, ta=False, splits=1):
+    M, K = (A.shape[1], A.shape[0]) if ta else A.shape
+    N = B.shape[1]
+    a.autotune_reset()
+    a.autotune_set(f"{'T' if ta else 'N'}N|{M}x{N}x{K}", cfg, splits)
+    ws = torch.empty(16 << 20, dtype=torch.uint8, device="cuda")
+    C = torch.empty((M, N), dtype=torch.float32, device="cuda")
+    a.gemm(to_dev(A), to_dev(B), C, ta, False, ws=ws)
+    return C.cpu().numpy()
+
+
+@pytest.mark.parametrize("cfg", CONFIGS)
+def test_split_gemm_keeps_the_bits_of_small_and_large_operands(cfg):
+    """Operands from FP32's subnormals to 1e37, with results in its normal range: bfloat16
+    thirds of an operand below 2^-110 would fall under bfloat16's smallest value."""
+    a = api()
+    rng = np.random.default_rng(cfg)
+    try:
+        for sa, sb in ((1e-34, 1.0), (1.0, 1e-36), (1e-37, 1e2), (1e3, 1e-39), (1e-40, 1e6), (1e-18, 1e-17),
+                       (1e-37, 1e37), (1e30, 1e-30), (1e34, 1e2), (1e18, 1e17)):
+            for ta, M, N, K in ((False, 70, 66, 96), (True, 40, 66, 129)):
+                A = (rng.standard_normal((K, M) if ta else (M, K)) * sa).astype(np.float32)
+                B = (rng.standard_normal((K, N)) * sb).astype(np.float32)
+                ref = (A.T if ta else A).astype(np.float64) @ B.astype(np.float64)
+                err = [np.linalg.norm((run(a, c, A, B, ta) - ref) / np.linalg.norm(ref)) for c in (0, cfg)]
+                assert err[1] <= max(err[0], 1e-7), (cfg, sa, sb, ta, err)
+    finally:
+        a.autotune_reset()
