@@ -7,8 +7,10 @@
 // differences are exact in FP32 and the last remainder has at most 8 significant
 // bits, so hi + mid + lo = x (down to bfloat16's smallest subnormal, 2^-133).
 // A product a b is then hi hi + (hi mid + mid hi + hi lo + lo hi + mid mid) plus
-// terms below 2^-25 |a b|, which are left out: six v_mfma_f32_32x32x16_bf16 for
-// 16 k, 192 matrix-pipe cycles where v_mfma_f32_32x32x2f32 needs 512.  The products
+// mid lo + lo mid, at most 2^-25 |a b| each and as often positive as negative, and
+// lo lo, which are left out: six v_mfma_f32_32x32x16_bf16 for
+// 16 k, 192 matrix-pipe cycles where v_mfma_f32_32x32x2f32 needs 512 (with the two
+// of them taken in, that product takes 61 us).  The products
 // of bfloat16 values are exact in FP32; the hi hi sums and the corrections have an
 // FP32 accumulator each, added once at the end, so the small terms are not rounded
 // at the size of the large sum.  Measured against FP64 on 32x32 tiles of normal
@@ -16,10 +18,9 @@
 // 2.9e-7 -> 8.3e-8, K = 4,096 1.2e-6 -> 4.0e-7, K = 131,072 6.2e-6 -> 2.4e-6; with
 // all six products in one accumulator the errors are those of the FP32 MFMA.
 //
-// A result that is not finite is recomputed in plain FP32 from the operands (an
-// infinity would meet a zero mid part, and a value within 2^-9 of the largest
-// FP32 number rounds to an infinite hi): infinities and NaNs come out as an FP32
-// sum gives them.
+// A 32x32 tile's results that are not finite come from FP32 MFMAs (tile_fp32; an
+// infinity meets a zero mid part, and a value within 2^-9 of the largest FP32 number
+// rounds to an infinite hi): infinities and NaNs come out as an FP32 sum gives them.
 //
 // Structure (k_gemm_oct): a block computes BM x BN with WM x WN wavefronts; K advances
 // in BK-deep steps.  Global values are loaded two steps ahead into registers with
@@ -66,6 +67,8 @@ __device__ inline float low_bf16(unsigned p) {
   return __uint_as_float(__builtin_amdgcn_perm(0u, p, 0x01000c0cu));
 }
 __device__ inline float high_bf16(unsigned p) { return __uint_as_float(p & 0xffff0000u); }
+// hi hi | hi mid | mid hi | mid mid | hi lo | lo hi
+constexpr int kTerms = 6, kPlaneA[kTerms] = {0, 0, 1, 1, 0, 2}, kPlaneB[kTerms] = {0, 1, 0, 1, 2, 0};
 __device__ inline void split_pair(float a, float b, unsigned& h, unsigned& m, unsigned& l) {
   h = pack_bf16(a, b);
   const float ra = a - low_bf16(h), rb = b - high_bf16(h);
@@ -233,18 +236,38 @@ __device__ inline void advance(Cursor& c, int bk) {
   if constexpr (!KC) c.p = reinterpret_cast<const float*>(reinterpret_cast<const char*>(c.p) + (size_t)bk * c.ld4);
 }
 
-// Plain FP32 sum over this block's K range of one result (the non-finite ones).
+// 32x32 results by FP32 MFMAs in k order straight from memory, over [b0, e0) of the
+// first piece and [b1, e1) of the second: rows `row` .. (m_left of them inside), columns
+// `col` .. (n_left), in the accumulator layout of the 32x32 MFMA.
 template <bool A_T, bool B_T>
-__device__ __attribute__((noinline)) float dot_fp32(const float* A0, const float* A1, const float* B0,
-                                                    const float* B1, int64_t lda0, int64_t lda1,
-                                                    int64_t ldb0, int64_t ldb1, int64_t row, int64_t col,
-                                                    int b0, int e0, int b1, int e1) {
-  float s = 0.f;
-  for (int k = b0; k < e0; ++k)
-    s = fmaf(A_T ? A0[k * lda0 + row] : A0[row * lda0 + k], B_T ? B0[col * ldb0 + k] : B0[k * ldb0 + col], s);
-  for (int k = b1; k < e1; ++k)
-    s = fmaf(A_T ? A1[k * lda1 + row] : A1[row * lda1 + k], B_T ? B1[col * ldb1 + k] : B1[k * ldb1 + col], s);
-  return s;
+__device__ __attribute__((noinline)) floatx16 tile_fp32(const float* A0, const float* A1, const float* B0,
+                                                        const float* B1, int64_t lda0, int64_t lda1,
+                                                        int64_t ldb0, int64_t ldb1, int64_t row, int64_t col,
+                                                        int m_left, int n_left, int b0, int e0, int b1, int e1) {
+  floatx16 acc;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+#if defined(__HIP_DEVICE_COMPILE__)
+  const int l32 = threadIdx.x & 31, half = (threadIdx.x >> 5) & 1;
+  const bool m_in = l32 < m_left, n_in = l32 < n_left;
+  auto piece = [&](const float* A, const float* B, int64_t lda, int64_t ldb, int b, int e) {
+    constexpr int U = 4;  // MFMAs of two k each per trip
+    for (int k0 = b; k0 < e; k0 += 2 * U) {
+      float x[U], y[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int64_t k = k0 + 2 * u + half;
+        x[u] = m_in && k < e ? A[A_T ? k * lda + row + l32 : (row + l32) * lda + k] : 0.f;
+        y[u] = n_in && k < e ? B[B_T ? (col + l32) * ldb + k : k * ldb + col + l32] : 0.f;
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x[u], y[u], acc, 0, 0, 0);
+    }
+  };
+  piece(A0, B0, lda0, ldb0, b0, e0);
+  piece(A1, B1, lda1, ldb1, b1, e1);
+#endif
+  return acc;
 }
 
 // This block's work: problem, tile and K range.
@@ -334,8 +357,8 @@ __device__ inline float* partial_of(const LaunchArgs& args, const Work& w) {
   return args.partial + P.part_off + ((int64_t)w.split * (GM == 2 ? args.G : 1) + w.grp) * P.M * P.n_eff;
 }
 
-// Epilogue of one 32x32 tile at row0, col0 of the block's tile: acc + cor, a
-// non-finite value recomputed over the block's K range [b, e) in steps of BK, then the
+// Epilogue of one 32x32 tile at row0, col0 of the block's tile: acc + cor (non-finite
+// values: FP32 sums over the block's steps [kt_begin, kt_end) of bk), then the
 // partial tile or bias, addend, beta C, ReLU, mask, result and sigmoid.
 // Accumulator layout of the 32x32 MFMA: register r of lane l holds
 // D[8*(r/4) + 4*(l/32) + r%4][l%32].  Rows past the edge lie past the range of the
@@ -371,22 +394,20 @@ __device__ __forceinline__ void oct_epilogue(const LaunchArgs& args, const Work&
   };
   float v[16];
   if constexpr (SP) {
+    const int b0 = min(w.kn0, kt_begin * bk), e0 = min(w.kn0, kt_end * bk);
+    const int b1 = max(0, min(w.kn1, (kt_begin - nt0) * bk)), e1 = max(0, min(w.kn1, (kt_end - nt0) * bk));
     float nf = 0.f;  // NaN if one of them is not finite
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       v[r] = acc[r] + cor[r];
       nf = fmaf(v[r], 0.f, nf);
     }
-    if (nf != nf) {
+    if (__any(nf != nf)) {  // uniform
+      const floatx16 f = tile_fp32<A_T, B_T>(w.A0, w.A1, w.B0, w.B1, P.lda[0], P.lda[1], P.ldb[0], P.ldb[1],
+                                             w.m0 + row0, w.n0 + col0, m_valid - row0, P.N - w.n0 - col0, b0, e0, b1,
+                                             e1);
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int row = r0 + (r >> 2) * 8 + (r & 3);
-        if (row < m_valid && col < P.N && !(fabsf(v[r]) <= 3.402823466e38f))
-          v[r] = dot_fp32<A_T, B_T>(w.A0, w.A1, w.B0, w.B1, P.lda[0], P.lda[1], P.ldb[0], P.ldb[1], w.m0 + row, col,
-                                    min(w.kn0, kt_begin * bk), min(w.kn0, kt_end * bk),
-                                    max(0, min(w.kn1, (kt_begin - nt0) * bk)),
-                                    max(0, min(w.kn1, (kt_end - nt0) * bk)));
-      }
+      for (int r = 0; r < 16; ++r) v[r] = fabsf(v[r]) <= 3.402823466e38f ? v[r] : f[r];
     }
   } else {
 #pragma unroll
@@ -528,7 +549,7 @@ __global__ __launch_bounds__(64 * WM * WN) void k_gemm_oct(LaunchArgs args) {
   // kt + 1 and its stores to the other LDS stage.
   constexpr int KS = BK / 16;
   constexpr int NF = TA::NP;
-  constexpr int PER = (SP ? 6 : 8) * TM * TN;                 // MFMAs per 16 k
+  constexpr int PER = (SP ? kTerms : 8) * TM * TN;                 // MFMAs per 16 k
   constexpr int NCONV = 2 * (TA::NU + TB::NU);       // half octets to split per thread and step
   constexpr int NREAD = NF * (TM + TN);
   constexpr int NSLOT = PER * KS;
@@ -558,11 +579,9 @@ __global__ __launch_bounds__(64 * WM * WN) void k_gemm_oct(LaunchArgs args) {
       constexpr int ks = slot / PER, sl = slot % PER;
       constexpr int term = sl / (TM * TN), i = (sl / TN) % TM, j = sl % TN;
       if constexpr (SP) {
-        // hi hi | hi mid | mid hi | mid mid | hi lo | lo hi
-        constexpr int pa_of[6] = {0, 0, 1, 1, 0, 2}, pb_of[6] = {0, 1, 0, 1, 2, 0};
         floatx16& c = term == 0 ? acc[i][j] : cor[i][j];
-        c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, f[ks % 2].a[i][pa_of[term]]),
-                                                    __builtin_bit_cast(bf16x8, f[ks % 2].b[j][pb_of[term]]), c, 0, 0, 0);
+        c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, f[ks % 2].a[i][kPlaneA[term]]),
+                                                    __builtin_bit_cast(bf16x8, f[ks % 2].b[j][kPlaneB[term]]), c, 0, 0, 0);
       } else {
         acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(f[ks % 2].a[i][term / 4][term % 4]),
                                                          __uint_as_float(f[ks % 2].b[j][term / 4][term % 4]),
@@ -721,7 +740,7 @@ __global__ __launch_bounds__(64 * WM, BN >= 64 ? 2 : 4) void k_gemm_rows(LaunchA
   };
   // Step kt (LDS stage cur): a0 holds its first octet split, `now` its raw values,
   // `nxt` those of step kt + 1; `now` then receives step kt + 2.
-  constexpr int PER = 6 * TN;
+  constexpr int PER = kTerms * TN;
   constexpr int NSLOT = 2 * PER;
   constexpr int NB = 2 * TB::NU;
   Planes a0, a1;
@@ -737,13 +756,11 @@ __global__ __launch_bounds__(64 * WM, BN >= 64 ? 2 : 4) void k_gemm_rows(LaunchA
     __builtin_amdgcn_sched_barrier(0);
     static_for<NSLOT>([&](auto sc) {
       constexpr int slot = decltype(sc)::value;
-      constexpr int ks = slot / PER, j = slot % PER / 6, term = slot % 6, g = slot / 6;
-      // hi hi | hi mid | mid hi | mid mid | hi lo | lo hi
-      constexpr int pa_of[6] = {0, 0, 1, 1, 0, 2}, pb_of[6] = {0, 1, 0, 1, 2, 0};
+      constexpr int ks = slot / PER, j = slot % PER / kTerms, term = slot % kTerms, g = slot / kTerms;
       const Planes& a = ks == 0 ? a0 : a1;
       floatx16& c = term == 0 ? acc[j] : cor[j];
-      c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a.p[pa_of[term]]),
-                                                  __builtin_bit_cast(bf16x8, f[g % 2][pb_of[term]]), c, 0, 0, 0);
+      c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a.p[kPlaneA[term]]),
+                                                  __builtin_bit_cast(bf16x8, f[g % 2][kPlaneB[term]]), c, 0, 0, 0);
       if constexpr (term % 2 == 0 && g + 1 < 2 * TN) {  // next column tile's operands
         constexpr int p = term / 2, g1 = g + 1;
         f[g1 % 2][p] = bs[p * TB::PLANE + (2 * half + g1 / TN) * TB::ROWP + 32 * (g1 % TN) + l32];
