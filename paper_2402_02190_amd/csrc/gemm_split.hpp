@@ -2,10 +2,13 @@
 // ones in the same structure.  Shared by
 // the translation units of the plain and the grouped launches; not part of the ABI.
 //
-// Every FP32 operand value x is written as hi + mid + lo, three bfloat16 values
-// rounded to nearest: hi = bf16(x), mid = bf16(x - hi), lo = x - hi - mid.  Both
+// Every FP32 operand value, times 2^16, is written as x = hi + mid + lo, three bfloat16
+// values rounded to nearest: hi = bf16(x), mid = bf16(x - hi), lo = x - hi - mid.  Both
 // differences are exact in FP32 and the last remainder has at most 8 significant
-// bits, so hi + mid + lo = x (down to bfloat16's smallest subnormal, 2^-133).
+// bits, so hi + mid + lo = x: the scaling puts the last bit of every FP32 number, 2^-149
+// and up, at or above bfloat16's smallest subnormal, 2^-133 (without it an operand of
+// 1e-35 kept 18 bits and one of 1e-37 11; it costs a product 1 to 3%: 100,000x128,
+// K = 256: 51.5 -> 52.4 us).
 // A product a b is then hi hi + (hi mid + mid hi + hi lo + lo hi + mid mid) plus
 // mid lo + lo mid, at most 2^-25 |a b| each and as often positive as negative, and
 // lo lo, which are left out: six v_mfma_f32_32x32x16_bf16 for
@@ -19,8 +22,8 @@
 // all six products in one accumulator the errors are those of the FP32 MFMA.
 //
 // A 32x32 tile's results that are not finite come from FP32 MFMAs (tile_fp32; an
-// infinity meets a zero mid part, and a value within 2^-9 of the largest FP32 number
-// rounds to an infinite hi): infinities and NaNs come out as an FP32 sum gives them.
+// infinity meets a zero mid part, operands from 2^112 on round to an infinite hi, and
+// scaled sums from 2^96 on overflow): large results, infinities and NaNs come out as an FP32 sum gives them.
 //
 // Structure (k_gemm_oct): a block computes BM x BN with WM x WN wavefronts; K advances
 // in BK-deep steps.  Global values are loaded two steps ahead into registers with
@@ -69,7 +72,10 @@ __device__ inline float low_bf16(unsigned p) {
 __device__ inline float high_bf16(unsigned p) { return __uint_as_float(p & 0xffff0000u); }
 // hi hi | hi mid | mid hi | mid mid | hi lo | lo hi
 constexpr int kTerms = 6, kPlaneA[kTerms] = {0, 0, 1, 1, 0, 2}, kPlaneB[kTerms] = {0, 1, 0, 1, 2, 0};
+constexpr float kScale = 0x1p16f, kUnscale = 0x1p-32f;  // of an operand, and back from a product of two
 __device__ inline void split_pair(float a, float b, unsigned& h, unsigned& m, unsigned& l) {
+  a *= kScale;
+  b *= kScale;
   h = pack_bf16(a, b);
   const float ra = a - low_bf16(h), rb = b - high_bf16(h);
   m = pack_bf16(ra, rb);
@@ -399,7 +405,7 @@ __device__ __forceinline__ void oct_epilogue(const LaunchArgs& args, const Work&
     float nf = 0.f;  // NaN if one of them is not finite
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      v[r] = acc[r] + cor[r];
+      v[r] = (acc[r] + cor[r]) * kUnscale;
       nf = fmaf(v[r], 0.f, nf);
     }
     if (__any(nf != nf)) {  // uniform

@@ -61,3 +61,22 @@ def test_split_gemm_with_a_near_maximal_value_in_every_sum(cfg):
                             assert np.allclose(*out, rtol=1e-5), (cfg, M, N, K, ta, tb)
     finally:
         a.autotune_reset()
+
+
+@pytest.mark.parametrize("cfg", CONFIGS)
+def test_split_gemm_keeps_the_bits_of_small_and_large_operands(cfg):
+    """Operands from FP32's subnormals to 1e37, with results in its normal range: bfloat16
+    thirds of an operand below 2^-110 would fall under bfloat16's smallest value."""
+    a = api()
+    rng = np.random.default_rng(cfg)
+    try:
+        for sa, sb in ((1e-34, 1.0), (1.0, 1e-36), (1e-37, 1e2), (1e3, 1e-39), (1e-40, 1e6), (1e-18, 1e-17),
+                       (1e-37, 1e37), (1e30, 1e-30), (1e34, 1e2), (1e18, 1e17)):
+            for ta, M, N, K in ((False, 70, 66, 96), (True, 40, 66, 129)):
+                A = (rng.standard_normal((K, M) if ta else (M, K)) * sa).astype(np.float32)
+                B = (rng.standard_normal((K, N)) * sb).astype(np.float32)
+                ref = (A.T if ta else A).astype(np.float64) @ B.astype(np.float64)
+                err = [np.linalg.norm((run(a, c, A, B, ta) - ref) / np.linalg.norm(ref)) for c in (0, cfg)]
+                assert err[1] <= max(err[0], 1e-7), (cfg, sa, sb, ta, err)
+    finally:
+        a.autotune_reset()
