@@ -19,11 +19,14 @@
 // at the size of the large sum.  Measured against FP64 on 32x32 tiles of normal
 // data (relative 2-norm; FP32 MFMA -> this): K = 32 1.1e-7 -> 3.9e-8, K = 256
 // 2.9e-7 -> 8.3e-8, K = 4,096 1.2e-6 -> 4.0e-7, K = 131,072 6.2e-6 -> 2.4e-6; with
-// all six products in one accumulator the errors are those of the FP32 MFMA.
+// all six products in one accumulator the errors are those of the FP32 MFMA.  The
+// largest error of a sum of K products, in 2^-24 of their magnitudes: K = 1 1.0 -> 1.8,
+// K = 2 1.9 -> 2.4, K = 3 2.6 -> 2.3, K = 8 4.0 -> 2.1, K = 32 5.0 -> 2.2; so a block
+// with one or two k takes FP32 MFMAs (tile_fp32).
 //
-// A 32x32 tile's results that are not finite come from FP32 MFMAs (tile_fp32; an
-// infinity meets a zero mid part, operands from 2^112 on round to an infinite hi, and
-// scaled sums from 2^96 on overflow): large results, infinities and NaNs come out as an FP32 sum gives them.
+// So does a 32x32 tile for its results that are not finite (an infinity meets a zero
+// mid part, operands from 2^112 on round to an infinite hi, and scaled sums from 2^96
+// on overflow): large results, infinities and NaNs come out as an FP32 sum gives them.
 //
 // Structure (k_gemm_oct): a block computes BM x BN with WM x WN wavefronts; K advances
 // in BK-deep steps.  Global values are loaded two steps ahead into registers with
@@ -73,6 +76,7 @@ __device__ inline float high_bf16(unsigned p) { return __uint_as_float(p & 0xfff
 // hi hi | hi mid | mid hi | mid mid | hi lo | lo hi
 constexpr int kTerms = 6, kPlaneA[kTerms] = {0, 0, 1, 1, 0, 2}, kPlaneB[kTerms] = {0, 1, 0, 1, 2, 0};
 constexpr float kScale = 0x1p16f, kUnscale = 0x1p-32f;  // of an operand, and back from a product of two
+constexpr int kBrief = 2;  // up to so many products in a sum, FP32's error is the smaller
 __device__ inline void split_pair(float a, float b, unsigned& h, unsigned& m, unsigned& l) {
   a *= kScale;
   b *= kScale;
@@ -363,8 +367,8 @@ __device__ inline float* partial_of(const LaunchArgs& args, const Work& w) {
   return args.partial + P.part_off + ((int64_t)w.split * (GM == 2 ? args.G : 1) + w.grp) * P.M * P.n_eff;
 }
 
-// Epilogue of one 32x32 tile at row0, col0 of the block's tile: acc + cor (non-finite
-// values: FP32 sums over the block's steps [kt_begin, kt_end) of bk), then the
+// Epilogue of one 32x32 tile at row0, col0 of the block's tile: acc + cor (or FP32 sums
+// over the block's steps [kt_begin, kt_end) of bk, see above), then the
 // partial tile or bias, addend, beta C, ReLU, mask, result and sigmoid.
 // Accumulator layout of the 32x32 MFMA: register r of lane l holds
 // D[8*(r/4) + 4*(l/32) + r%4][l%32].  Rows past the edge lie past the range of the
@@ -402,18 +406,19 @@ __device__ __forceinline__ void oct_epilogue(const LaunchArgs& args, const Work&
   if constexpr (SP) {
     const int b0 = min(w.kn0, kt_begin * bk), e0 = min(w.kn0, kt_end * bk);
     const int b1 = max(0, min(w.kn1, (kt_begin - nt0) * bk)), e1 = max(0, min(w.kn1, (kt_end - nt0) * bk));
+    const bool brief = e0 - b0 + e1 - b1 <= kBrief;
     float nf = 0.f;  // NaN if one of them is not finite
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       v[r] = (acc[r] + cor[r]) * kUnscale;
       nf = fmaf(v[r], 0.f, nf);
     }
-    if (__any(nf != nf)) {  // uniform
+    if (brief || __any(nf != nf)) {  // uniform
       const floatx16 f = tile_fp32<A_T, B_T>(w.A0, w.A1, w.B0, w.B1, P.lda[0], P.lda[1], P.ldb[0], P.ldb[1],
                                              w.m0 + row0, w.n0 + col0, m_valid - row0, P.N - w.n0 - col0, b0, e0, b1,
                                              e1);
 #pragma unroll
-      for (int r = 0; r < 16; ++r) v[r] = fabsf(v[r]) <= 3.402823466e38f ? v[r] : f[r];
+      for (int r = 0; r < 16; ++r) v[r] = !brief && fabsf(v[r]) <= 3.402823466e38f ? v[r] : f[r];
     }
   } else {
 #pragma unroll

@@ -80,3 +80,44 @@ def test_split_gemm_keeps_the_bits_of_small_and_large_operands(cfg):
                 assert err[1] <= max(err[0], 1e-7), (cfg, sa, sb, ta, err)
     finally:
         a.autotune_reset()
+
+
+@pytest.mark.parametrize("cfg", CONFIGS)
+def test_split_gemm_of_one_or_two_products_per_sum(cfg):
+    """Sums of one and two products, where the terms that the splitting leaves out count
+    for more than FP32's rounding: the bits of the FP32 loop.  Tiles' edges, all layouts;
+    and graphs of one and two rows among larger ones."""
+    a = api()
+    rng = np.random.default_rng(cfg)
+    try:
+        for K in (1, 2):
+            for M, N in ((130, 66), (7, 33)):
+                for ta in (False, True):
+                    for tb in (False, True):
+                        A = rng.standard_normal((K, M) if ta else (M, K)).astype(np.float32)
+                        B = rng.standard_normal((N, K) if tb else (K, N)).astype(np.float32)
+                        out = []
+                        for c in (0, cfg):
+                            a.autotune_reset()
+                            a.autotune_set(f"{'T' if ta else 'N'}{'T' if tb else 'N'}|{M}x{N}x{K}", c, 1)
+                            C = torch.empty((M, N), dtype=torch.float32, device="cuda")
+                            a.gemm(to_dev(A), to_dev(B), C, ta, tb)
+                            out.append(C.cpu().numpy())
+                        assert np.array_equal(*out), (cfg, K, M, N, ta, tb)
+        ptr = np.array([0, 1, 3, 40, 41], np.int32)
+        n, G, M, N = 41, 4, 40, 24
+        dg = a.DeviceGraph(np.zeros(n + 1, np.int32), np.zeros(0, np.int32), None, ptr)
+        A = rng.standard_normal((n, M)).astype(np.float32)
+        B = rng.standard_normal((n, N)).astype(np.float32)
+        out = []
+        for c in (0, cfg):
+            a.autotune_reset()
+            a.autotune_set(f"TN|g2:{G}|{M}x{N + 1}x{n}", c, 1)
+            C = torch.full((G, M, N), np.nan, dtype=torch.float32, device="cuda")
+            bg = torch.full((G, M), np.nan, dtype=torch.float32, device="cuda")
+            a.gemm_grouped_k(dg, to_dev(A), to_dev(B), C, bg, ws=torch.empty(1 << 20, dtype=torch.uint8, device="cuda"))
+            out.append(C.cpu().numpy())
+        for g in (0, 1, 3):
+            assert np.array_equal(out[0][g], out[1][g]), (cfg, "graph", g)
+    finally:
+        a.autotune_reset()
