@@ -561,7 +561,11 @@ cpra_status cpra_graph_destroy(cpra_graph graph);
  * caller's workspace; the fastest is recorded and its result left in C.
  * Tuning synchronises the stream; launches on a stream being captured and
  * GEMMs with beta != 0 are never tuned.  Later calls with a tuned shape use
- * the recorded plan, others a fixed heuristic.  autotune_get reads entry i:
+ * the recorded plan, others a fixed heuristic.  The heuristic sums a training
+ * step's products in FP32 in the order of k; a plan that the tuning of another
+ * call recorded (cpra_gemm, a forward) does not change that, one that a tuned
+ * step recorded or autotune_set inserted replaces it, and may be of any
+ * kind (three-way bfloat16 splitting among them).  autotune_get reads entry i:
  * the shape key, the chosen configuration index and split count, their name
  * "config/splitN", its time and the time of the heuristic plan (microseconds).
  * ---------------------------------------------------------------------- */

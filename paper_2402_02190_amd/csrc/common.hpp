@@ -236,8 +236,8 @@ struct GemmProblem {
   const int32_t* group_ptr;  // [n_groups + 1] graph row offsets (device; mode 2)
   const GroupRows* rows;     // row tiles (mode 1)
   int64_t b_stride, c_stride, bias_stride, bg_stride;
-  // Sum over k in order with FP32 MFMAs (the untuned plan of a training step, whose
-  // FP64 loss terms then do not depend on the tile shape).
+  // Sum over k in order with FP32 MFMAs unless a tuned step or the caller's table says
+  // otherwise (a training step, whose FP64 loss terms then do not depend on the tile shape).
   bool ordered;
 };
 

@@ -174,6 +174,12 @@ int heuristic_splits(const GemmProblem* probs, int n, const Cfg& c) {
   return max(1, min(s, kMaxSplits));
 }
 
+bool any_ordered(const GemmProblem* probs, int n) {
+  for (int i = 0; i < n; ++i)
+    if (probs[i].ordered) return true;
+  return false;
+}
+
 // The plan of a shape that is not in the tuning table (us alone, three launches
 // between two events, against the 64x64x32 or 128x128x32 one-deep loop that these
 // rules replace and the best of configurations 0-31).
@@ -195,11 +201,11 @@ int heuristic_splits(const GemmProblem* probs, int n, const Cfg& c) {
 //    up to 32 rows of output, 32-row tiles.
 Plan heuristic_plan(bool a_t, const GemmProblem* probs, int n, bool can_split) {
   int n_cols = 0, m_rows = 0;
-  bool ordered = false, bias_grad = false;
+  const bool ordered = any_ordered(probs, n);
+  bool bias_grad = false;
   for (int i = 0; i < n; ++i) {
     n_cols = max(n_cols, probs[i].N);
     m_rows = max(m_rows, probs[i].M);
-    ordered = ordered || probs[i].ordered;
     bias_grad = bias_grad || probs[i].bias_grad;
   }
   const int64_t tiles64 = tiles_of(probs, n, kCfgs[kOrd64]);
@@ -268,10 +274,14 @@ size_t partial_floats(int splits, const GemmProblem* probs, int n) {
 }
 
 // ---- tuning table -----------------------------------------------------------
+// `general`: tuned by a product that did not ask for ordered sums (GemmProblem::ordered).
+// Those that do pass over it, so that a training step's sums do not depend on what else
+// of the same shape was tuned before; their own tuning replaces it.
 struct TuneEntry {
   Plan plan;
   double us;
   double heuristic_us;
+  bool general;
 };
 
 std::mutex g_tune_mu;
@@ -296,10 +306,10 @@ std::string shape_key(bool a_t, bool b_t, const GemmProblem* probs, int n) {
   return k;
 }
 
-bool lookup(const std::string& key, Plan* out) {
+bool lookup(const std::string& key, bool ordered, Plan* out) {
   std::lock_guard<std::mutex> lk(g_tune_mu);
   auto it = g_table.find(key);
-  if (it == g_table.end()) return false;
+  if (it == g_table.end() || (ordered && it->second.general)) return false;
   *out = it->second.plan;
   return true;
 }
@@ -408,7 +418,7 @@ cpra_status tune(bool a_t, bool b_t, const GemmProblem* probs, int n, void* ws, 
   const Plan heur = heuristic_plan(a_t, probs, n, ws != nullptr);
   const char* env = getenv("CPRA_AUTOTUNE_LOG");  // print every candidate's time
   const bool log_candidates = env != nullptr && env[0] == '1';
-  TuneEntry entry{Plan{0, 1}, 1e30, -1.0};
+  TuneEntry entry{Plan{0, 1}, 1e30, -1.0, !any_ordered(probs, n)};
   for (int c = 0; c < kNumCfgs; ++c) {
     if (a_t && c >= kFirstRows && c < kFirstOrdered) continue;  // those take A [M, K]
     std::vector<int> splits;
@@ -497,7 +507,7 @@ cpra_status gemm_batch(bool a_t, bool b_t, const GemmProblem* probs_in, int n, v
   const bool can_split = ws != nullptr && ws_bytes > 0;
   const std::string key = shape_key(a_t, b_t, probs, n);
   Plan pl;
-  if (!lookup(key, &pl)) {
+  if (!lookup(key, any_ordered(probs, n), &pl)) {
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     const bool capturing =
         hipStreamIsCapturing(stream, &cs) == hipSuccess && cs != hipStreamCaptureStatusNone;
@@ -607,7 +617,7 @@ cpra_status cpra_autotune_set(const char* key, int32_t cfg, int32_t splits) {
     CPRA_FAIL(CPRA_ERR_PARAM, "autotune_set: config %d / splits %d out of range", cfg, splits);
   std::lock_guard<std::mutex> lk(g_tune_mu);
   if (g_table.find(key) == g_table.end()) g_order.push_back(key);
-  g_table[key] = TuneEntry{Plan{cfg, splits}, -1.0, -1.0};
+  g_table[key] = TuneEntry{Plan{cfg, splits}, -1.0, -1.0, false};
   return CPRA_OK;
 }
 
