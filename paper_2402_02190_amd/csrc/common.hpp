@@ -239,6 +239,7 @@ struct GemmProblem {
   // Sum over k in order with FP32 MFMAs unless a tuned step or the caller's table says
   // otherwise (a training step, whose FP64 loss terms then do not depend on the tile shape).
   bool ordered;
+  bool halves;  // two products side by side, N / 2 columns each (saved tuning tables name them so)
 };
 
 // Up to 4 independent problems in one launch, all with the same operand layout.

@@ -314,6 +314,17 @@ bool lookup(const std::string& key, bool ordered, Plan* out) {
   return true;
 }
 
+// The entry of a launch: under its own key or, where two products of the same rows of A
+// became one (GemmProblem::halves), under the key that the two had in earlier tables.
+bool find_plan(bool a_t, bool b_t, const GemmProblem* probs, int n, const std::string& key, Plan* out) {
+  const bool ordered = any_ordered(probs, n);
+  if (lookup(key, ordered, out)) return true;
+  if (n != 1 || !probs[0].halves) return false;
+  GemmProblem two[2] = {probs[0], probs[0]};
+  two[0].N = two[1].N = probs[0].N / 2;
+  return lookup(shape_key(a_t, b_t, two, 2), ordered, out);
+}
+
 void fill_args(const GemmProblem* probs, int n, int splits, void* ws, LaunchArgs* args) {
   *args = LaunchArgs{};
   const GemmProblem& q0 = probs[0];
@@ -507,7 +518,7 @@ cpra_status gemm_batch(bool a_t, bool b_t, const GemmProblem* probs_in, int n, v
   const bool can_split = ws != nullptr && ws_bytes > 0;
   const std::string key = shape_key(a_t, b_t, probs, n);
   Plan pl;
-  if (!lookup(key, any_ordered(probs, n), &pl)) {
+  if (!find_plan(a_t, b_t, probs, n, key, &pl)) {
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     const bool capturing =
         hipStreamIsCapturing(stream, &cs) == hipSuccess && cs != hipStreamCaptureStatusNone;

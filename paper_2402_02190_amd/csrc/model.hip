@@ -283,6 +283,7 @@ cpra_status forward_impl(const cpra_csr* g, const Plan& p, const float* params, 
         q[i].ldc = ldyy;
         q[i].M = N;
         q[i].N = n_prob == 1 ? 2 * l.out : l.out;
+        q[i].halves = n_prob == 1;
         set_groups(p, g, &rows, 1, &q[i], l);
         q[i].ordered = ordered;
       }

@@ -71,3 +71,27 @@ def test_an_inserted_plan_holds_for_a_step(cfg, name):
     finally:
         api.autotune_reset()
         sol.close()
+
+
+def test_a_saved_entry_of_two_products_holds_for_the_one_they_became():
+    """Earlier tables name the two products of a linear-first layer (H Ws^T and H Wn^T)
+    side by side; their entry is found by the product of both."""
+    need_gpu()
+    from paper_2402_02190_amd import api
+    from paper_2402_02190_amd.solver import CPRAConfig, CPRASolver
+    from workloads import random_regular_graph
+    n, hidden, S = 3000, 64, 16
+    sol = CPRASolver(api.DeviceGraph.from_csr(random_regular_graph(n, 4, 3)), CPRAConfig("mis", "gcn", 1, hidden, S),
+                     np.logspace(-1, 1, S).astype(np.float32))
+    one, two = f"NT|{n}x{2 * S}x{hidden}", f"NT|{n}x{S}x{hidden}|{n}x{S}x{hidden}"
+    try:
+        for entries, family in (({two: 3}, "gemm_nt_128x64x32_w2x2"), ({two: 3, one: 10}, "gemm_nt_64x64x16_w2x2_p2")):
+            api.autotune_reset()
+            for k, cfg in entries.items():
+                api.autotune_set(k, cfg, 1)
+            for call in (sol.forward, sol.step):
+                fam = families(api, call)
+                assert family in fam, (entries, sorted(fam))
+    finally:
+        api.autotune_reset()
+        sol.close()
