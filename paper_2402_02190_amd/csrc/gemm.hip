@@ -384,7 +384,8 @@ cpra_status run_plan(bool a_t, bool b_t, const GemmProblem* probs, int n, const 
   LaunchArgs args;
   fill_args(probs, n, pl.splits, ws, &args);
   // the configuration that runs (and names the profiler family)
-  const int cfg = resolve_cfg(args, a_t, b_t, pl.cfg);
+  const int mode = probs[0].group_mode;
+  const int cfg = resolve_cfg(args, a_t, b_t, mode, pl.cfg);
   double flops = 0, red_bytes = 0;
   for (int i = 0; i < n; ++i) {
     const double mn = (double)args.p[i].M * args.p[i].N;
@@ -394,7 +395,6 @@ cpra_status run_plan(bool a_t, bool b_t, const GemmProblem* probs, int n, const 
   // profiler family = one kernel instantiation: layout + group mode + tile configuration
   static const char* layout[2][2] = {{"nn", "nt"}, {"tn", "tt"}};
   static const char* gmode[3] = {"", "_byrow", "_byk"};
-  const int mode = probs[0].group_mode;
   char pname[64];
   snprintf(pname, sizeof(pname), "gemm_%s%s_%s", layout[a_t][b_t], gmode[mode], kCfgNames[cfg]);
   {
@@ -430,8 +430,11 @@ cpra_status tune(bool a_t, bool b_t, const GemmProblem* probs, int n, void* ws, 
   const char* env = getenv("CPRA_AUTOTUNE_LOG");  // print every candidate's time
   const bool log_candidates = env != nullptr && env[0] == '1';
   TuneEntry entry{Plan{0, 1}, 1e30, -1.0, !any_ordered(probs, n)};
+  LaunchArgs args;
+  fill_args(probs, n, 1, nullptr, &args);
+  auto resolved = [&](int c) { return resolve_cfg(args, a_t, b_t, probs[0].group_mode, c); };
   for (int c = 0; c < kNumCfgs; ++c) {
-    if (a_t && c >= kFirstRows && c < kFirstOrdered) continue;  // those take A [M, K]
+    if (resolved(c) != c) continue;  // another one's kernel, timed as that
     std::vector<int> splits;
     for (int s : split_candidates(probs, n, kCfgs[c]))
       if (s == 1 || (ws != nullptr && partial_floats(s, probs, n) * sizeof(float) <= ws_bytes))
@@ -449,7 +452,7 @@ cpra_status tune(bool a_t, bool b_t, const GemmProblem* probs, int n, void* ws, 
       const double us = 1e3 * ms / reps;
       if (log_candidates)
         fprintf(stderr, "[cpra autotune] %s %s/split%d %.2f us\n", key.c_str(), kCfgNames[c], s, us);
-      if (c == heur.cfg && s == heur.splits) entry.heuristic_us = us;
+      if (c == resolved(heur.cfg) && s == heur.splits) entry.heuristic_us = us;
       if (us < entry.us) {
         entry.us = us;
         entry.plan = pl;

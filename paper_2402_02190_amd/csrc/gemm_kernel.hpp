@@ -1034,7 +1034,7 @@ constexpr int kFirstSplit = 32;  // configurations from here on are those of gem
 constexpr int kFirstRows = 40;   // ... and from here on take A [M, K] (k_gemm_rows)
 constexpr int kSplit64 = 32, kSplit32x64 = 37, kSplit32 = 38, kRows128x64 = 41, kRows128x32 = 42, kRows32 = 44;
 constexpr int kFirstOrdered = 45;  // FP32 MFMAs, sums over k in order
-constexpr int kOrd64 = 45, kOrd128x64 = 46, kOrd32x64 = 47, kOrd32 = 48, kOrd128x32 = 50, kDirect = 51;
+constexpr int kOrd64 = 45, kOrd32x64 = 47, kOrd32 = 48, kOrd128x32 = 50, kDirect = 51;
 
 // index of a row-tile height in LaunchArgs::row_maps
 constexpr int bm_index(int bm) { return bm == 32 ? 0 : bm == 64 ? 1 : 2; }
@@ -1128,14 +1128,24 @@ inline bool ring_ok(const LaunchArgs& args, bool a_t, bool b_t) {
   return true;
 }
 
-// The configuration that runs for a requested one: the one-deep twin where the
+// The configuration that runs for a requested one (mode: GemmProblem::group_mode).
+// 32 and up: 64x64 tiles in place of A in registers where A is stored [K, M], 32-row
+// tiles in place of the direct ones for grouped products, those with a bias gradient and
+// those of more rows than its grid holds, and a plain loop past the split kernels'
+// offsets.  Below: the one-deep twin where the
 // branch-free loads may not run, the two-deep twin where the interleaved or
 // ring loop would need a bias gradient, the interleaved twin where the ring's
 // offsets would not reach.
 bool split_ok(const LaunchArgs& args);  // gemm.hip
-inline int resolve_cfg(const LaunchArgs& args, bool a_t, bool b_t, int cfg) {
+inline int resolve_cfg(const LaunchArgs& args, bool a_t, bool b_t, int mode, int cfg) {
   if (cfg < 0 || cfg >= kNumCfgs) return cfg;
   if (cfg >= kFirstSplit) {
+    if (a_t && cfg >= kFirstRows && cfg < kFirstOrdered) cfg = kSplit64;
+    if (cfg == kDirect) {
+      bool fits = !mode && !wants_bias_grad(args);
+      for (int i = 0; i < args.n_prob; ++i) fits = fits && args.p[i].M <= 16 * 65535;
+      if (!fits) cfg = kOrd32x64;
+    }
     if (split_ok(args)) return cfg;
     cfg = cfg >= kFirstOrdered ? 0 : 20;
   }
@@ -1147,7 +1157,7 @@ inline int resolve_cfg(const LaunchArgs& args, bool a_t, bool b_t, int cfg) {
 
 template <bool A_T, bool B_T, int GM>
 void launch_any(int cfg, LaunchArgs& args, hipStream_t stream) {
-  cfg = resolve_cfg(args, A_T, B_T, cfg);
+  cfg = resolve_cfg(args, A_T, B_T, GM, cfg);
   switch (cfg) {
 #define CPRA_GEMM_CFG(I, BM, BN, BK, WM, WN, PF) \
   case I: launch_cfg<BM, BN, BK, WM, WN, A_T, B_T, PF, GM>(args, stream); break;

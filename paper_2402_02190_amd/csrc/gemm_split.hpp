@@ -1011,46 +1011,34 @@ void launch_oct(LaunchArgs& args, hipStream_t stream) {
   hipLaunchKernelGGL((k_gemm_oct<BM, BN, BK, WM, WN, A_T, B_T, true, SP, GM>), grid, block, 0, stream, args);
 }
 
-template <int BN, int WM, bool A_T, bool B_T, int GM>
+template <int BN, int WM, bool B_T, int GM>
 void launch_rows(LaunchArgs& args, hipStream_t stream) {
-  if constexpr (A_T) {  // A is not K-contiguous: the tile of the same columns
-    launch_oct<64, 64, 32, 2, 2, true, A_T, B_T, GM>(args, stream);
-  } else {
-    const dim3 grid = split_grid<32 * WM, BN, GM>(args), block(64 * WM);
-    if (split_vec(args, A_T, B_T))
-      hipLaunchKernelGGL((k_gemm_rows<BN, WM, B_T, true, GM>), grid, block, 0, stream, args);
-    else
-      hipLaunchKernelGGL((k_gemm_rows<BN, WM, B_T, false, GM>), grid, block, 0, stream, args);
-  }
+  const dim3 grid = split_grid<32 * WM, BN, GM>(args), block(64 * WM);
+  if (split_vec(args, false, B_T))
+    hipLaunchKernelGGL((k_gemm_rows<BN, WM, B_T, true, GM>), grid, block, 0, stream, args);
+  else
+    hipLaunchKernelGGL((k_gemm_rows<BN, WM, B_T, false, GM>), grid, block, 0, stream, args);
 }
 
-// Grouped products, those with a bias gradient and the tallest ones take the 32-row tiles instead.
-template <bool A_T, bool B_T, int GM>
+template <bool A_T, bool B_T>
 void launch_direct(LaunchArgs& args, hipStream_t stream) {
-  if constexpr (GM == 0) {
-    int64_t rows = 0;
-    for (int i = 0; i < args.n_prob; ++i) rows = std::max<int64_t>(rows, args.p[i].M);
-    if (!wants_bias_grad(args) && rows <= 16 * 65535) {  // the grid's limit
-      int tm = 0, tn = 0;
-      for (int i = 0; i < args.n_prob; ++i) {
-        ProbDev& d = args.p[i];
-        d.tiles_m = (int)ceil_div(d.M, 16);
-        d.tiles_n = (int)ceil_div(d.N, 16);
-        tm = max(tm, d.tiles_m);
-        tn = max(tn, d.tiles_n);
-      }
-      args.grid_x = tn;
-      const dim3 grid((unsigned)(tn * args.n_prob), (unsigned)tm, (unsigned)args.splits);
-      if (split_vec(args, A_T, B_T))
-        hipLaunchKernelGGL((k_gemm_direct<A_T, B_T, true>), grid, dim3(64), 0, stream, args);
-      else
-        hipLaunchKernelGGL((k_gemm_direct<A_T, B_T, false>), grid, dim3(64), 0, stream, args);
-      return;
-    }
+  int tm = 0, tn = 0;
+  for (int i = 0; i < args.n_prob; ++i) {
+    ProbDev& d = args.p[i];
+    d.tiles_m = (int)ceil_div(d.M, 16);
+    d.tiles_n = (int)ceil_div(d.N, 16);
+    tm = max(tm, d.tiles_m);
+    tn = max(tn, d.tiles_n);
   }
-  launch_oct<32, 64, 32, 1, 2, false, A_T, B_T, GM>(args, stream);
+  args.grid_x = tn;
+  const dim3 grid((unsigned)(tn * args.n_prob), (unsigned)tm, (unsigned)args.splits);
+  if (split_vec(args, A_T, B_T))
+    hipLaunchKernelGGL((k_gemm_direct<A_T, B_T, true>), grid, dim3(64), 0, stream, args);
+  else
+    hipLaunchKernelGGL((k_gemm_direct<A_T, B_T, false>), grid, dim3(64), 0, stream, args);
 }
 
+// cfg as resolve_cfg gives it.
 template <bool A_T, bool B_T, int GM>
 void launch_split_any(int cfg, LaunchArgs& args, hipStream_t stream) {
   switch (cfg) {
@@ -1071,13 +1059,17 @@ void launch_split_any(int cfg, LaunchArgs& args, hipStream_t stream) {
     CPRA_SPLIT_CFG(49, 128, 128, 32, 2, 4, false)
     CPRA_SPLIT_CFG(50, 128, 32, 32, 4, 1, false)
 #undef CPRA_SPLIT_CFG
-    case 40: launch_rows<128, 4, A_T, B_T, GM>(args, stream); break;
-    case 41: launch_rows<64, 4, A_T, B_T, GM>(args, stream); break;
-    case 42: launch_rows<32, 4, A_T, B_T, GM>(args, stream); break;
-    case 43: launch_rows<64, 2, A_T, B_T, GM>(args, stream); break;
-    case 44: launch_rows<32, 1, A_T, B_T, GM>(args, stream); break;
-    case kDirect: launch_direct<A_T, B_T, GM>(args, stream); break;
-    default: break;
+    default:
+      if constexpr (!A_T) {
+        if (cfg == 40) launch_rows<128, 4, B_T, GM>(args, stream);
+        if (cfg == 41) launch_rows<64, 4, B_T, GM>(args, stream);
+        if (cfg == 42) launch_rows<32, 4, B_T, GM>(args, stream);
+        if (cfg == 43) launch_rows<64, 2, B_T, GM>(args, stream);
+        if (cfg == 44) launch_rows<32, 1, B_T, GM>(args, stream);
+      }
+      if constexpr (GM == 0) {
+        if (cfg == kDirect) launch_direct<A_T, B_T>(args, stream);
+      }
   }
 }
 
