@@ -284,20 +284,17 @@ cpra_status early_stop_update(const cpra_csr* g, const cpra_loss_cfg* lc, const 
                               const cpra_early_stop_cfg* es, int32_t* counter, hipStream_t stream);
 cpra_status check_adam_cfg(const cpra_adam_cfg* cfg);
 
-// Side stream of the current device (see streams.hip).  fork_to makes the side
-// stream wait for everything enqueued so far on `main`; join_from makes `main`
-// wait for everything enqueued so far on the side stream.  fork_mark +
-// fork_wait is fork_to in two halves: the side stream waits for what `main` had
-// enqueued at the mark, so main-stream work enqueued between the two is
-// captured ahead of the side work (in a captured graph the main chain then
-// keeps its hardware queue) without the side work waiting for it.
+// Side stream of the current device (see streams.hip).  At fork_wait the side stream
+// waits for what `main` had enqueued at fork_mark, so main-stream work enqueued between
+// the two is captured ahead of the side work (in a captured graph the main chain then
+// keeps its hardware queue) without the side work waiting for it; join_from makes
+// `main` wait for everything enqueued so far on the side stream.
 struct SideStream {
   hipStream_t stream;
   hipEvent_t ev[2];
 };
 // Null outside captures and with CPRA_OVERLAP=0 in the environment.
 cpra_status side_stream_for(hipStream_t main, SideStream** out);
-cpra_status fork_to(SideStream* s, hipStream_t main);
 cpra_status fork_mark(SideStream* s, hipStream_t main);
 cpra_status fork_wait(SideStream* s);
 cpra_status join_from(SideStream* s, hipStream_t main);

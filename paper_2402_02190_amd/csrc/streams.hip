@@ -41,10 +41,13 @@ cpra_status get_side_stream(SideStream** out) {
 // The side stream for work enqueued on `main`, or null: it forks in a captured graph,
 // where a fork is an edge between nodes (a step of a 3-layer network, N = 100,000:
 // 1.24 ms, on one stream 1.26; 10,000 nodes, 2x256: 0.214 and 0.225).  An eager fork and
-// join cost 25 to 40 us of event traffic between the streams, more than the overlap
-// gives: backward of one layer of 128 columns, 2,000 nodes 61 us and 25, 100,000 nodes
-// 252 and 227; two layers of 256, 10,000 nodes 104 and 110.  The environment is read at
-// every call, so that a caller can capture either kind.
+// join cost 20 to 80 us of event traffic between the streams, which the overlap rarely
+// pays for.  Eager steps, forked and on one stream, us: 3 layers of 128, N = 100,000 1,204
+// and 1,173; 2x256, N = 10,000 209 and 206; 4 layers of 128, N = 50,000 638 and 618;
+// 6 layers of 64, N = 20,000 372 and 316.  A backward alone: 637 and 593; 103 and 106;
+// 284 and 308; 281 and 198; over 52 shapes of one to three layers 0.96 to 1.35 times as
+// long with the fork, with no order in depth or size.  The environment is read at every
+// call, so that a caller can capture either kind.
 cpra_status side_stream_for(hipStream_t main, SideStream** out) {
   *out = nullptr;
   const char* e = getenv("CPRA_OVERLAP");
@@ -54,13 +57,6 @@ cpra_status side_stream_for(hipStream_t main, SideStream** out) {
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
   if (main != nullptr && hipStreamIsCapturing(main, &cs) == hipSuccess && cs == hipStreamCaptureStatusActive)
     *out = side;  // (the null stream cannot be captured)
-  return CPRA_OK;
-}
-
-cpra_status fork_to(SideStream* s, hipStream_t main) {
-  hipError_t e = hipEventRecord(s->ev[0], main);
-  if (e == hipSuccess) e = hipStreamWaitEvent(s->stream, s->ev[0], 0);
-  if (e != hipSuccess) CPRA_FAIL(CPRA_ERR_HIP, "fork: %s", hipGetErrorString(e));
   return CPRA_OK;
 }
 
