@@ -60,12 +60,14 @@ class ProfScope {
   size_t idx_ = 0;
 };
 
-// 1 / x for x in [1, 2] (or NaN), rounded like the division: the reciprocal's estimate
-// corrected by its own residual, without the scaling and fix-up that the general
-// division needs (equal for every such x).
+// 1 / x for x in [1, 2] (or NaN), rounded like the division: the reciprocal's estimate (one
+// unit in the last place) corrected by its own residual, without the scaling and fix-up
+// that the general division needs.  That gives the division's result for every x but
+// the last below 2, whose estimate 0.5 would be left at a tie.
 __device__ __forceinline__ float recip_1_2(float x) {
   const float r = __builtin_amdgcn_rcpf(x);
-  return fmaf(fmaf(-x, r, 1.0f), r, r);
+  const float y = fmaf(fmaf(-x, r, 1.0f), r, r);
+  return x == 0x1.fffffep0f ? 0x1.000002p-1f : y;
 }
 
 inline hipStream_t as_stream(cpra_stream_t s) { return reinterpret_cast<hipStream_t>(s); }
