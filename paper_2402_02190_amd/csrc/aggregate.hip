@@ -95,14 +95,16 @@ struct AggArgs {
   int32_t* queue;  // persistent launches: the work queue (kQueueInts counters)
   int units;       // persistent launches: row blocks of 4 wavefronts
   int chunk;       // persistent launches: row blocks per dequeue
-  int stream_out;  // streaming output stores and index loads (tables larger than L2)
+  int stream_out;  // streaming output stores (tables larger than L2)
 };
 
 // A streaming (nontemporal) store of one VEC-float vector.  Above kStreamOutBytes of
 // output (more than the 8 XCDs' L2 together) the output rows, which this launch does
 // not read again, are stored this way so that they take no L2 lines from the gathered
-// table, and the index stream is read the same way: C3 (a 182 MB table) 1.775 ->
-// 1.751 ms per step, C4 (51 MB) and C3s (22 MB) unchanged; on C2 (10 MB) it cost 0.8%.
+// table: C3 (a 182 MB table) 1.775 -> 1.751 ms per step, C4 (51 MB) and C3s (22 MB)
+// unchanged; on C2 (10 MB) it cost 0.8%.  The index stream goes the same way with 64-bit
+// addresses only: by buffer loads (NARROW) it is kept, as the slices of a row read it
+// again (100,000 x 128, 20-regular: 145 us nontemporal, 103 kept).
 template <int VEC>
 __device__ inline void store_nt(const typename Vec<VEC>::T& v, float* p) {
   if constexpr (VEC == 1) {

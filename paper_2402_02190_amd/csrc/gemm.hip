@@ -1,7 +1,8 @@
 // FP32 GEMM on the CDNA matrix cores (v_mfma_f32_32x32x2f32) for the GNN's
 // dense weight products: forward X W^T, input gradient dY W and weight
-// gradient dY^T X.  The kernel template is in gemm_kernel.hpp; this file
-// holds the plain instantiations, planning, autotuning and the entry points.
+// gradient dY^T X.  The kernel templates are in gemm_kernel.hpp and gemm_split.hpp, their
+// instantiations in gemm_plain.hip, gemm_grouped.hip and gemm_split_*.hip; this file
+// holds planning, autotuning, the split-K reduction and the entry points.
 //
 // One launch runs up to four independent problems.
 // A problem's contraction may be split in two K pieces with separate
@@ -192,8 +193,10 @@ bool any_ordered(const GemmProblem* probs, int n) {
 //    704,000x64, K = 64: 76, 86, 190, 111), 64x64 below (10,000x256, K = 512: 25.5,
 //    ordered 31, 128x64 rows 27, before 46, best old 35).
 //  * The smallest of those (alone, back to back in a graph): one 16x16 tile per
-//    wavefront.  Up to 512 tiles: 100x64, K = 64: 4.4, ordered 4.5; 500x64, K = 128: 5.5
-//    and 5.9; 2,000x64, K = 128: 5.7 and 5.95; 4,000x64, K = 64: 5.0 and 4.7.  Weight
+//    wavefront.  100x64, K = 64: 4.4, ordered 4.5; 500x64, K = 128: 5.5 and 5.9;
+//    2,000x64, K = 128: 5.7 and 5.95; 4,000x64, K = 64: 5.0 and 4.7.  But up to 64 tiles
+//    only: inside a step the neighbouring launches hide that gain (a step of two layers
+//    of 2,000x64: 115 to 120 with the limit at 512 tiles, 114 at 64).  Weight
 //    gradients up to 2,048 tiles and splits: 32x64 over K = 100: 4.6 and 5.6; 64x64 over
 //    1,000 with 8 splits: 6.8 and 8.2.
 //  * Weight gradients: the split count brings 64x64 tiles to 512 blocks with 4 K steps
