@@ -315,7 +315,12 @@ int64_t cpra_model_param_count(const cpra_model_cfg* cfg, int32_t n_nodes);
 cpra_status cpra_model_param_offsets(const cpra_model_cfg* cfg, int32_t n_nodes, int64_t* offsets);
 /* Bytes of activation storage kept from forward to backward plus backward scratch. */
 size_t cpra_model_workspace_bytes(const cpra_csr* g, const cpra_model_cfg* cfg);
-/* Z [N,S] (ldz >= S).  Saves the activations the backward needs in ws. */
+/* Z [N,S] (ldz >= S).  Saves the activations the backward needs in ws.
+ * Z is that of a training step on the same parameters to FP32 rounding (about
+ * 1e-7 of its norm), not to the bit: the step sums its products in order, the
+ * forward as is fastest.  With a frozen prefix (train_from_layer > 0), whose
+ * activations a step may reuse, and where a table entry that holds for the step
+ * names every product's plan, both run the same kernels. */
 cpra_status cpra_model_forward(const cpra_csr* g, const cpra_model_cfg* cfg, const float* params,
                                float* Z, int64_t ldz, void* ws, size_t ws_bytes,
                                cpra_stream_t stream);

@@ -333,7 +333,8 @@ class CPRASolver:
         return done
 
     def forward(self, stream=None) -> torch.Tensor:
-        """Z = GNN(params) without a parameter update."""
+        """Z = GNN(params) without a parameter update: a step's logits to FP32 rounding (see
+        cpra_model_forward)."""
         api.model_forward(self.graph, self.model_cfg, self.params, self.Z, self.ws, stream)
         return self.Z
 
