@@ -92,10 +92,9 @@ def steps(trace_dir: str, bench_json: str, title: str, command: str, out: str) -
 
 
 def _sweep_kernel(name: str):
-    if "k_loss<" in name:
-        return "loss_fwd_bwd"
-    if "k_aggregate<" in name and "false>" in name:
-        return "aggregate"
+    for family in ("loss_fwd_bwd", "aggregate"):
+        if kernel_pattern(family).search(name):
+            return family
     return None
 
 
