@@ -183,7 +183,8 @@ bool any_ordered(const GemmProblem* probs, int n) {
 
 // The plan of a shape that is not in the tuning table (us alone, three launches
 // between two events, against the 64x64x32 or 128x128x32 one-deep loop that these
-// rules replace and the best of configurations 0-31).
+// rules replace and the best of configurations 0-31; the split kernels' times are from
+// before their operands were scaled, which adds 1 to 3%).
 //  * Ordered products (a training step's) and small launches: FP32 MFMAs over k in
 //    order, 64x64 tiles, or 32 rows where those leave fewer than 128 blocks.  Under
 //    256 blocks the matrix rate does not set the time and both kinds take the same

@@ -38,12 +38,14 @@
 // [k octet][row][8], each octet's rows followed by 128 / OCT bytes, so that the operand
 // reads (32 consecutive rows of one octet) and the stores (consecutive rows of one
 // octet, or 8 / OCT rows of all octets) meet every bank once.  The splitting of the
-// next tile (5.5 VALU instructions per value) is placed between the MFMAs of the
+// next tile (6.5 VALU instructions per value) is placed between the MFMAs of the
 // current one.  What bounds it is a wavefront's instruction issue (one VALU
 // instruction per 5-8 cycles, so the loop is kept lean: cursors in scalar registers,
-// no selects at the edges) and, at K <= 64, memory.  100,000x128, K = 256, NT: 57 us
-// with 64x64 tiles, 49 (134 TFLOP/s) with A in registers (k_gemm_rows) against 78-97
-// for the FP32 loops of gemm_kernel.hpp; matrix pipe busy 43%.
+// no selects at the edges) and, at K <= 64, memory.  100,000x128, K = 256, NT: 58 us
+// with 64x64 tiles, 50 (131 TFLOP/s) with A in registers (k_gemm_rows) against 78-97
+// for the FP32 loops of gemm_kernel.hpp; matrix pipes busy 22 to 32% of the time in the
+// products of a step over 100,000 nodes.  (Remainders by v_dot2_f32_bf16 take 4.5
+// instructions per value, but 1 to 10% more time.)
 //
 // The same structure without splitting (SP = false) feeds v_mfma_f32_32x32x2f32 with k
 // in order, which gives the bits of the one- and two-deep loops of gemm_kernel.hpp for
