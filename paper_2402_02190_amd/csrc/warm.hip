@@ -124,9 +124,12 @@ __device__ __forceinline__ int wedges_by_compare(const int32_t* __restrict__ row
 // of the graph apart, so that a run of large ones is spread over as many wavefronts.
 //
 // Bound by the chain of dependent loads while the wavefronts fit the chip, then by the
-// comparisons.  16 lanes per node from 8,192 nodes on and up to a mean degree of 24, else
-// a wavefront per node (us, 16 lanes and 64; before both, by search alone, in brackets):
-//   5-regular    8,000 8.2, 7.9 (7.8); 32,000 8.1, 16.2 (22.8); 200,000 34, 89 (178)
+// comparisons.  16 lanes per node from 8,192 nodes on up to a mean degree of 24, from
+// 4,096 on up to 12, else a wavefront per node (us, 16 lanes and 64; before both, by
+// search alone, in brackets; the first three rows back to back in a graph):
+//   3-regular    2,000 3.7, 3.3; 5,000 3.9, 4.2; 20,000 5.2, 9.2
+//   5-regular    500 3.9, 3.4; 5,000 4.2, 4.6; 12,000 4.8, 7.3; 50,000 11.5, 22
+//   10-regular   2,000 6.2, 5.5; 5,000 6.6, 7.8; 20,000 10.2, 20
 //   16-regular   8,000 10.6, 14.9 (19.9); 32,000 30, 42 (67)
 //   20-regular   2,000 19.9, 10.8 (16.0); 8,000 22.7, 23.1 (26.4); 32,000 55, 68 (91)
 //   40-regular   2,000 96, 27 (39); 32,000 232, 204 (332)
@@ -162,7 +165,8 @@ __global__ __launch_bounds__(256) void k_node_features(int n, const int32_t* __r
 #pragma unroll
     for (int off = 8; off > 0; off >>= 1) cnt += __shfl_xor(cnt, off);
   }
-  for (int t = 0; t < NPW; ++t) {
+  const bool wide = LPN == 64 || __any(d > 32);
+  for (int t = 0; wide && t < NPW; ++t) {
     const int dt = __shfl(d, LPN * t);  // uniform, as the branches on it
     if (LPN == 16 && dt <= 32) continue;
     const int bt = __shfl(b, LPN * t);
@@ -856,7 +860,8 @@ cpra_status cpra_node_features(const cpra_csr* g, int32_t in_dim, int32_t n_rand
                        (triangles ? 8.0 : 0.0) * g->n_nodes + 4.0 * (double)g->nnz +
                        4.0 * (g->n_nodes + 1.0);
   ProfScope ps("node_features", st, 0.0, bytes);
-  const bool four = g->n_nodes >= 8192 && g->nnz <= 24 * (int64_t)g->n_nodes;
+  const int64_t n = g->n_nodes;
+  const bool four = (n >= 8192 && g->nnz <= 24 * n) || (n >= 4096 && g->nnz <= 12 * n);
   auto* const kernel = four ? k_node_features<16> : k_node_features<64>;
   hipLaunchKernelGGL(kernel, dim3((unsigned)ceil_div(g->n_nodes, four ? 16 : 4)), dim3(256), 0, st,
                      g->n_nodes, g->row_ptr, g->col_idx, in_dim, n_rand, rand, ld_rand, feat,

@@ -18,7 +18,7 @@ def ring_edges(first, n, d):
     return first + u, first + (u + np.tile(np.arange(1, d // 2 + 1), n)) % n
 
 
-@pytest.mark.parametrize("n", [8191, 8192, 8195])
+@pytest.mark.parametrize("n", [4095, 4096, 8191, 8192, 8195])
 @pytest.mark.parametrize("large", [(34, 48, 50), (100,), (16, 32)])
 def test_features_of_large_nodes_among_small_ones(n, large):
     """Rings of the large degrees side by side at the graph's start and at its end, a
