@@ -95,3 +95,44 @@ def test_a_saved_entry_of_two_products_holds_for_the_one_they_became():
     finally:
         api.autotune_reset()
         sol.close()
+
+
+def test_a_forward_gives_a_steps_logits():
+    """To FP32 rounding by themselves; to the bit when a table names every product, and
+    with a frozen prefix."""
+    api, sol, p = setup()
+    try:
+        api.autotune_reset()
+        sol.load_params(p)
+        sol.autotune()
+        keys = [e["key"] for e in api.autotune_table()]
+        for table in (False, True):
+            api.autotune_reset()
+            if table:
+                for k in keys:
+                    api.autotune_set(k, 32, 1)
+            sol.load_params(p)
+            sol.step()
+            Z = sol.Z.clone()
+            sol.load_params(p)
+            sol.forward()
+            rel = float((sol.Z - Z).double().norm() / Z.double().norm())
+            assert rel <= 1e-6, rel
+            assert not table or torch.equal(sol.Z, Z)
+    finally:
+        api.autotune_reset()
+        sol.close()
+    from paper_2402_02190_amd.solver import CPRAConfig, CPRASolver
+    from workloads import init_params, random_regular_graph
+    n, S = 30000, 64
+    frozen = CPRASolver(api.DeviceGraph.from_csr(random_regular_graph(n, 5, 3)),
+                        CPRAConfig("mis", "gcn", 2, 128, S, train_from_layer=1),
+                        np.logspace(-1, 1, S).astype(np.float32))
+    try:
+        frozen.load_params(init_params("gcn", n, 2, 128, S, seed=2))
+        frozen.forward()
+        Z = frozen.Z.clone()
+        frozen.step()
+        assert torch.equal(frozen.Z, Z)
+    finally:
+        frozen.close()
